@@ -6,10 +6,10 @@
 // one-wave finalize kernel merges the block partials in a fixed order and
 // writes log Z-hat = LSE - log N, the ESS and the posterior summaries.
 //
-// Data rows are the same for every lane of a wave (all lanes process the same
-// datum for different particles), so they are read with scalar loads into
-// SGPRs and used directly as the scalar operand of v_fma_f32; per-particle
-// state stays in VGPRs for the whole data loop.
+// Data are the same for every lane of a wave (all lanes process the same datum
+// for different particles): scalar loads bring them into SGPRs, and the rows of
+// the linear regression into the matrix operand; per-particle state stays in
+// VGPRs for the whole data loop.
 #include "blr.h"
 #include "device.h"
 #include "host.h"
@@ -24,60 +24,156 @@ constexpr int kIsWaves = kIsThreads / 64;
 constexpr int kPolyNF = 29;     // summary fields of the polynomial model
 
 // ------------------------------------------------------------------ BLR --
+// The residuals r = y_d - x_d . w of a particle set are a matrix product, and
+// run on the matrix cores: v_mfma_f32_4x4x1_16b_f32 multiplies, in each of its
+// 16 blocks, 4 rows of A by 4 columns of B with one term of the sum, so lane l
+// holds one particle (column) and gets four data rows in its four results.
+// A's values of one block are broadcast to all blocks (CBSZ = 4, ABID = block),
+// so one register per column k holds the k-th entry of 64 data rows, one row
+// per lane, loaded once per 64 rows with whole cache lines.
+// Why this shape: one term per instruction makes each result the chain
+// fma(-x_k, w_k, r), k in order, that a lane would compute by itself, in the
+// same FP32 rounding (checked bit for bit, subnormals, infinities and NaN
+// included), and all rows of a particle stay in its lane, so the FP32 sums of
+// squares within 32 rows keep their order too.  The matrix cores take FP32 at
+// 256 FLOP per cycle and CU, the vector units at 128 without packed FP32.
+// Measured at 2^20 particles x 10^4 rows, d = 16: 2.67 ms a call against 4.89 for
+// the same chain on the vector units (0.95 of their rate), 134 of the matrix
+// cores' 157 TFLOP/s.  Bound: matrix-core issue; the squares run beside it.
+typedef float blr_f32x4 __attribute__((ext_vector_type(4)));
+typedef float blr_row4 __attribute__((ext_vector_type(4), aligned(4)));   // data rows are 4-byte aligned
+
+// Adds the squared residuals of row groups B .. E - 1 (four rows each) of the
+// rows in a to s, G groups at a time: G P independent chains hide the latency
+// of the dependent products.
+template <int P, int DIM, int G, int B, int E>
+__device__ __forceinline__ void blr_row_groups(const float (&a)[DIM], const float *__restrict__ Y,
+                                               const float (&w)[P][DIM], float (&s)[P]) {
+    if constexpr (B < E) {
+        static_assert(G == 1 || G == 4, "row groups per step");
+        blr_f32x4 r[G][P];
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+#pragma unroll
+            for (int p = 0; p < P; ++p)
+                r[g][p] = blr_f32x4{Y[4 * (B + g)], Y[4 * (B + g) + 1], Y[4 * (B + g) + 2], Y[4 * (B + g) + 3]};
+#pragma unroll
+        for (int k = 0; k < DIM; ++k)
+#pragma unroll
+            for (int p = 0; p < P; ++p) {
+                r[0][p] = __builtin_amdgcn_mfma_f32_4x4x1f32(a[k], w[p][k], r[0][p], 4, B, 0);
+                if constexpr (G == 4) {
+                    r[1][p] = __builtin_amdgcn_mfma_f32_4x4x1f32(a[k], w[p][k], r[1][p], 4, B + 1, 0);
+                    r[2][p] = __builtin_amdgcn_mfma_f32_4x4x1f32(a[k], w[p][k], r[2][p], 4, B + 2, 0);
+                    r[3][p] = __builtin_amdgcn_mfma_f32_4x4x1f32(a[k], w[p][k], r[3][p], 4, B + 3, 0);
+                }
+            }
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int p = 0; p < P; ++p) s[p] = fmaf(r[g][p][i], r[g][p][i], s[p]);
+        blr_row_groups<P, DIM, G, B + G, E>(a, Y, w, s);
+    }
+}
+
+// Lane l's row d + l (rows past the last are not used: the last one is read
+// again), negated.
+template <int DIM>
+__device__ __forceinline__ void blr_load_rows(const float *__restrict__ X, int d, int last, float (&a)[DIM]) {
+    const blr_row4 *row = (const blr_row4 *)(X + (size_t)min(d + (int)(threadIdx.x & 63), last) * DIM);
+#pragma unroll
+    for (int q = 0; q < DIM / 4; ++q) {
+        const blr_row4 v = row[q];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) a[4 * q + e] = -v[e];
+    }
+}
+
 // Likelihood of one particle set: FP32 residuals r = y_d - x_d . w and squared
 // sums in FP32 within consecutive 32-row blocks; block sums accumulate in FP64.
-template <int P, int DIM, bool PROP>
-__global__ __launch_bounds__(kIsThreads) void blr_is_kernel(
+// The workgroup's 64 NW threads are S slices of NW / S waves: every slice holds
+// the same particles, P per lane, and takes one contiguous share of the rows
+// (in units of 64); the slices' FP64 sums are added in order through LDS.
+template <int P, int DIM, bool PROP, int S, int NW>
+__global__ __launch_bounds__(64 * NW, NW == 16 ? 4 : (PROP ? 2 : 3)) void blr_is_kernel(
     const float *__restrict__ X, const float *__restrict__ Y, int D, int64_t N, Key key,
     float prior_sd, double noise_sd, const float *__restrict__ qp, double *__restrict__ lw_out,
     float *__restrict__ lat_out, double *__restrict__ part) {
-    const int tid = threadIdx.x;
-    const int64_t base = (int64_t)blockIdx.x * (kIsThreads * P);
+    constexpr int kLanes = 64 * NW / S;      // particles of one index p
+    const int tid = threadIdx.x % kLanes;
+    const int slice = S == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x / kLanes);
+    const int64_t base = (int64_t)blockIdx.x * (kLanes * P);
 
     float w[P][DIM];
     double extra[P];
-    blr_draw<P, DIM, PROP, kIsThreads>(base, tid, key, prior_sd, qp, w, extra);
+    blr_draw<P, DIM, PROP, kLanes>(base, tid, key, prior_sd, qp, w, extra);
 
     double acc[P];
 #pragma unroll
     for (int p = 0; p < P; ++p) acc[p] = 0.0;
-    int d = 0;
-    for (; d + 32 <= D; d += 32) {
-        float s[P];
+    constexpr int G = P == 1 ? 4 : 1;
+    const int tiles = D / 64;
+    const int per = (tiles + S - 1) / S;
+    const int d1 = 64 * min(tiles, (slice + 1) * per);
+    int d = 64 * min(tiles, slice * per);
+    for (; d < d1; d += 64) {
+        float a[DIM];
+        blr_load_rows<DIM>(X, d, D - 1, a);
+        float s0[P], s1[P];
 #pragma unroll
-        for (int p = 0; p < P; ++p) s[p] = 0.0f;
-#pragma unroll 8
-        for (int dd = 0; dd < 32; ++dd) {
-            const float *row = X + (size_t)(d + dd) * DIM;
-            const float yv = Y[d + dd];
+        for (int p = 0; p < P; ++p) s0[p] = s1[p] = 0.0f;
+        blr_row_groups<P, DIM, G, 0, 8>(a, Y + d, w, s0);
+        blr_row_groups<P, DIM, G, 8, 16>(a, Y + d, w, s1);
 #pragma unroll
-            for (int p = 0; p < P; ++p) {
-                float r = yv;
-#pragma unroll
-                for (int k = 0; k < DIM; ++k) r = fmaf(-row[k], w[p][k], r);
-                s[p] = fmaf(r, r, s[p]);
-            }
+        for (int p = 0; p < P; ++p) {
+            acc[p] += (double)s0[p];
+            acc[p] += (double)s1[p];
         }
-#pragma unroll
-        for (int p = 0; p < P; ++p) acc[p] += (double)s[p];
     }
-    if (d < D) {
-        float s[P];
+    if (slice == S - 1) {                    // the rows after the last 64
+        d = 64 * tiles;
+        if (d + 32 <= D) {
+            float a[DIM], s[P];
+            blr_load_rows<DIM>(X, d, D - 1, a);
 #pragma unroll
-        for (int p = 0; p < P; ++p) s[p] = 0.0f;
-        for (; d < D; ++d) {
-            const float *row = X + (size_t)d * DIM;
-            const float yv = Y[d];
+            for (int p = 0; p < P; ++p) s[p] = 0.0f;
+            blr_row_groups<P, DIM, G, 0, 8>(a, Y + d, w, s);
 #pragma unroll
-            for (int p = 0; p < P; ++p) {
-                float r = yv;
-#pragma unroll
-                for (int k = 0; k < DIM; ++k) r = fmaf(-row[k], w[p][k], r);
-                s[p] = fmaf(r, r, s[p]);
-            }
+            for (int p = 0; p < P; ++p) acc[p] += (double)s[p];
+            d += 32;
         }
+        if (d < D) {
+            float s[P];
 #pragma unroll
-        for (int p = 0; p < P; ++p) acc[p] += (double)s[p];
+            for (int p = 0; p < P; ++p) s[p] = 0.0f;
+            for (; d < D; ++d) {
+                const float *row = X + (size_t)d * DIM;
+                const float yv = Y[d];
+#pragma unroll
+                for (int p = 0; p < P; ++p) {
+                    float r = yv;
+#pragma unroll
+                    for (int k = 0; k < DIM; ++k) r = fmaf(-row[k], w[p][k], r);
+                    s[p] = fmaf(r, r, s[p]);
+                }
+            }
+#pragma unroll
+            for (int p = 0; p < P; ++p) acc[p] += (double)s[p];
+        }
+    }
+    if constexpr (S > 1) {
+        __shared__ double sums[S - 1][kLanes * P];
+        if (slice > 0) {
+#pragma unroll
+            for (int p = 0; p < P; ++p) sums[slice - 1][p * kLanes + tid] = acc[p];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < S - 1; ++q)
+#pragma unroll
+            for (int p = 0; p < P; ++p) acc[p] += sums[q][p * kLanes + tid];
     }
 
     const double var = noise_sd * noise_sd;
@@ -85,7 +181,8 @@ __global__ __launch_bounds__(kIsThreads) void blr_is_kernel(
     double lw[P];
 #pragma unroll
     for (int p = 0; p < P; ++p) lw[p] = cterm - acc[p] / (2.0 * var) + extra[p];
-    blr_finish<P, DIM, kIsThreads, kIsWaves>(base, tid, N, w, lw, lw_out, lat_out, part);
+    // slice 0 holds the particles; the others add nothing to the record
+    blr_finish<P, DIM, kLanes, NW>(base, tid, slice == 0 ? N : 0, w, lw, lw_out, lat_out, part);
 }
 
 // ----------------------------------------------------------------- POLY --
@@ -199,17 +296,41 @@ size_t is_partial_bytes(int model, int dim, int64_t N) {
     return (size_t)blocks * (4 + nf) * sizeof(double) + merge_scratch_bytes(nf);
 }
 
-template <int DIM>
-static int launch_blr(const IsArgs &a, double *part, int64_t blocks, hipStream_t st) {
-    constexpr int P = 4;
+// Launch shape of blr_is_kernel.  The largest calls fill the chip with four
+// particles per lane and no split; below that the rows are split over the waves
+// of a workgroup, and at the smallest N a lane holds one particle, so that
+// 1000 waves or more share the work (n = 10^4 rows, d = 16, us a call before and
+// now: 1664 and 67 at 1000 particles, 1687 and 346 at 10^5; 768 and 354 at
+// 262144 x 5000 rows).  Splitting repeats the draw of the latents
+// in every slice, so it needs rows enough to pay for that (5000 x 200 rows
+// without it: 50 and 16 us).
+// A shape's workgroups never exceed those of (P = 4, S = 1) by more than
+// kMergeGroups, so its records fit where the second merge level's would be
+// (is_partial_bytes), which up to kMergeDirect records are not used.
+struct BlrShape {
+    int P, S, NW;
+};
+static BlrShape blr_shape(int64_t N, int64_t D) {
+    if (N <= 8192 && D >= 1024) return {1, 16, 16};
+    if (N <= 32768 && D >= 512) return {1, 4, 4};
+    if (N <= 131072) return D >= 512 ? BlrShape{4, 4, 4} : BlrShape{1, 1, 4};
+    if (N <= 524288 && D >= 512) return {4, 2, 4};
+    return {4, 1, 4};
+}
+
+template <int DIM, int P, int S, int NW>
+static int launch_blr_shape(const IsArgs &a, double *part, hipStream_t st) {
+    constexpr int64_t kPer = (int64_t)64 * NW / S * P;
+    const int64_t blocks = (a.N + kPer - 1) / kPer;
+    if (int rc = check_grid("blr_is_kernel", blocks, 64 * NW)) return rc;
     KernelTimer timer("blr_is_kernel", st);
     if (a.q_params)
-        hipLaunchKernelGGL((blr_is_kernel<P, DIM, true>), dim3((unsigned)blocks), dim3(kIsThreads), 0, st,
+        hipLaunchKernelGGL((blr_is_kernel<P, DIM, true, S, NW>), dim3((unsigned)blocks), dim3(64 * NW), 0, st,
                            (const float *)a.x, (const float *)a.y, (int)a.D, a.N, make_key(a.seed),
                            (float)a.hyper[0], a.hyper[1], (const float *)a.q_params, (double *)a.lw_out,
                            (float *)a.lat_out, part);
     else
-        hipLaunchKernelGGL((blr_is_kernel<P, DIM, false>), dim3((unsigned)blocks), dim3(kIsThreads), 0, st,
+        hipLaunchKernelGGL((blr_is_kernel<P, DIM, false, S, NW>), dim3((unsigned)blocks), dim3(64 * NW), 0, st,
                            (const float *)a.x, (const float *)a.y, (int)a.D, a.N, make_key(a.seed),
                            (float)a.hyper[0], a.hyper[1], nullptr, (double *)a.lw_out, (float *)a.lat_out, part);
     timer.stop();
@@ -221,6 +342,16 @@ static int launch_blr(const IsArgs &a, double *part, int64_t blocks, hipStream_t
                        (int)PPL_MODEL_BLR, a.scalars, a.summaries);
     PPL_LAUNCH_CHECK("weights_finalize_kernel");
     return PPL_OK;
+}
+
+template <int DIM>
+static int launch_blr(const IsArgs &a, hipStream_t st) {
+    const BlrShape s = blr_shape(a.N, a.D);
+    if (s.S == 16) return launch_blr_shape<DIM, 1, 16, 16>(a, a.part, st);
+    if (s.P == 1) return s.S == 4 ? launch_blr_shape<DIM, 1, 4, 4>(a, a.part, st) : launch_blr_shape<DIM, 1, 1, 4>(a, a.part, st);
+    if (s.S == 4) return launch_blr_shape<DIM, 4, 4, 4>(a, a.part, st);
+    if (s.S == 2) return launch_blr_shape<DIM, 4, 2, 4>(a, a.part, st);
+    return launch_blr_shape<DIM, 4, 1, 4>(a, a.part, st);
 }
 
 static int launch_poly(const IsArgs &a, hipStream_t st) {
@@ -247,14 +378,11 @@ int run_importance(const IsArgs &a, hipStream_t st) {
     if (a.model == PPL_MODEL_POLY) {
         return launch_poly(a, st);
     }
-    constexpr int P = 4;
-    const int64_t blocks = (a.N + kIsThreads * P - 1) / (kIsThreads * P);
-    if (int rc = check_grid("blr_is_kernel", blocks, kIsThreads)) return rc;
     switch (a.dim) {
-        case 4: return launch_blr<4>(a, a.part, blocks, st);
-        case 8: return launch_blr<8>(a, a.part, blocks, st);
-        case 12: return launch_blr<12>(a, a.part, blocks, st);
-        case 16: return launch_blr<16>(a, a.part, blocks, st);
+        case 4: return launch_blr<4>(a, st);
+        case 8: return launch_blr<8>(a, st);
+        case 12: return launch_blr<12>(a, st);
+        case 16: return launch_blr<16>(a, st);
     }
     return fail(PPL_E_ARG, "BLR dim must be 4, 8, 12 or 16 (got %d)", a.dim);
 }

@@ -1,0 +1,72 @@
+"""GPU parity at the sizes where a kernel changes its launch shape or runs a
+remainder: edges of tiles, row and particle counts on both sides of a rule.
+
+Tolerances are stated per test and follow from the arithmetic: what a shape
+cannot change is compared bit for bit, FP64 sums in another order within their
+rounding, FP32 values against the FP64 oracle within the FP32 class (1e-5).
+"""
+import numpy as np
+import pytest
+
+import synthetic
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ppl():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2010_08454_amd as p
+    return p
+
+
+# ------------------------------------------------- BLR on the matrix cores --
+def _blr(ppl, X, y, n, seed):
+    import torch
+    d = X.shape[1]
+    data = ppl.make_data(torch.from_numpy(X).cuda(), torch.from_numpy(y).cuda(), dim=d)
+    lw = torch.empty(n, dtype=torch.float64, device="cuda")
+    lat = torch.empty((d, n), dtype=torch.float32, device="cuda")
+    scal = torch.empty(8, dtype=torch.float64, device="cuda")
+    ppl.ppl_importance(ppl.PPL_MODEL_BLR, data, n, seed, log_weights=lw, latents=lat, scalars=scal)
+    return lw.cpu().numpy(), lat.cpu().numpy(), scal.cpu().numpy()
+
+
+@pytest.mark.parametrize("D", [1, 31, 32, 33, 63, 64, 95, 100, 511, 512, 1023, 1024, 1087])
+@pytest.mark.parametrize("dim", [4, 8, 12, 16])
+def test_blr_shapes(ppl, orc, D, dim):
+    """Row counts around the 64-row tiles, the 32-row blocks and the split
+    rules; particle counts on both sides of each rule.  Residuals and their
+    32-row sums do not depend on the shape; only the FP64 sum over the blocks
+    (all of one sign) may be taken in another order, so each particle's
+    log-weight agrees between shapes within (D / 32 + 16) 2^-52 of its
+    likelihood sum (bounded by |lw| + D |log(2 pi var)| / 2)."""
+    X, y, _ = synthetic.blr_data(D=D, d=dim, seed=70 + D)
+    seed, big = 11, 524_289
+    ref_lw, ref_lat, _ = _blr(ppl, X, y, big, seed)
+    idx = np.array([0, 1, 63, 64, 255, 256, 8191, 8192, 131_071, 524_287, 524_288])
+    rlw, _ = orc.particle_logweights(orc.MODEL_BLR, X, y, idx, seed, dim=dim)
+    assert np.max(np.abs(ref_lw[idx] - rlw) / np.maximum(1.0, np.abs(rlw))) < 1e-5
+    eps = (D / 32 + 16) * 2.0 ** -52
+    for n in (1, 65, 8192, 8193, 32_768, 32_769, 131_072, 131_073):
+        lw, lat, scal = _blr(ppl, X, y, n, seed)
+        np.testing.assert_array_equal(lat, ref_lat[:, :n])
+        assert np.all(np.abs(lw - ref_lw[:n]) <= eps * (np.abs(ref_lw[:n]) + D)), (n, D, dim)
+        m = lw.max()
+        assert abs(scal[0] - (m + np.log(np.exp(lw - m).sum()) - np.log(n))) <= 1e-10 * max(1.0, abs(scal[0]))
+
+
+@pytest.mark.parametrize("n", [100, 20_000, 100_000, 200_000, 600_000])
+@pytest.mark.parametrize("row", [0, 31, 700, 1050])
+def test_blr_nonfinite_rows(ppl, n, row):
+    """An infinite entry gives every particle zero weight and a NaN one makes
+    every log-weight NaN, whichever part of the data loop holds the row."""
+    X, y, _ = synthetic.blr_data(D=1060, d=16, seed=5)
+    for value, status in ((np.inf, ppl.PPL_E_ZERO_WEIGHT), (np.nan, ppl.PPL_E_NONFINITE)):
+        Xb = X.copy()
+        Xb[row, 7] = value
+        lw, _, scal = _blr(ppl, Xb, y, n, 3)
+        assert scal[3] == status
+        assert np.all(np.isneginf(lw)) if value == np.inf else np.all(np.isnan(lw))
