@@ -152,13 +152,8 @@ static int launch_blr_stats(const IsArgs &a, hipStream_t st) {
         timer.stop();
     }
     PPL_LAUNCH_CHECK("blr_stats_is_kernel");
-    int nrec = 0;
-    const double *rec = merge_partials_first<DIM>(part, blocks, part + (size_t)blocks * (4 + DIM), &nrec, st);
-    PPL_LAUNCH_CHECK("partial_merge_kernel");
-    hipLaunchKernelGGL(weights_finalize_kernel<DIM>, dim3(1), dim3(kFinalizeThreads), 0, st, rec, nrec, a.N,
-                       (int)PPL_MODEL_BLR, a.scalars, a.summaries);
-    PPL_LAUNCH_CHECK("weights_finalize_kernel");
-    return PPL_OK;
+    return finalize_weights<DIM>(part, blocks, part + (size_t)blocks * (4 + DIM), a.N, (int)PPL_MODEL_BLR, a.scalars,
+                                a.summaries, st);
 }
 
 int run_importance_blr_stats(const IsArgs &a, hipStream_t st) {

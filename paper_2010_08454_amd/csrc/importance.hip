@@ -21,7 +21,6 @@ namespace ppl {
 
 constexpr int kIsThreads = 256;
 constexpr int kIsWaves = kIsThreads / 64;
-constexpr int kPolyNF = 29;     // summary fields of the polynomial model
 
 // ------------------------------------------------------------------ BLR --
 // The residuals r = y_d - x_d . w of a particle set are a matrix product, and
@@ -281,8 +280,7 @@ __global__ __launch_bounds__(kIsThreads) void poly_is_kernel(
 #pragma unroll
                 for (int j = 0; j < 5; ++j) pp.f[4 + 5 * s + j] += sel * pc[p][j];
             }
-#pragma unroll
-            for (int j = 0; j < 5; ++j) pp.f[24 + j] += e * pc[p][j];
+            pp.f[24] += k < 0 ? e * pc[p][0] : 0.0;
         }
     }
     partial_block_reduce_store<kPolyNF, kIsWaves>(pp, part + (size_t)blockIdx.x * (4 + kPolyNF));
@@ -335,13 +333,8 @@ static int launch_blr_shape(const IsArgs &a, double *part, hipStream_t st) {
                            (float)a.hyper[0], a.hyper[1], nullptr, (double *)a.lw_out, (float *)a.lat_out, part);
     timer.stop();
     PPL_LAUNCH_CHECK("blr_is_kernel");
-    int nrec = 0;
-    const double *rec = merge_partials_first<DIM>(part, blocks, part + (size_t)blocks * (4 + DIM), &nrec, st);
-    PPL_LAUNCH_CHECK("partial_merge_kernel");
-    hipLaunchKernelGGL(weights_finalize_kernel<DIM>, dim3(1), dim3(kFinalizeThreads), 0, st, rec, nrec, a.N,
-                       (int)PPL_MODEL_BLR, a.scalars, a.summaries);
-    PPL_LAUNCH_CHECK("weights_finalize_kernel");
-    return PPL_OK;
+    return finalize_weights<DIM>(part, blocks, part + (size_t)blocks * (4 + DIM), a.N, (int)PPL_MODEL_BLR, a.scalars,
+                                a.summaries, st);
 }
 
 template <int DIM>
@@ -364,14 +357,8 @@ static int launch_poly(const IsArgs &a, hipStream_t st) {
                        (int)a.hyper[2], (double *)a.lw_out, (double *)a.lat_out, a.part);
     timer.stop();
     PPL_LAUNCH_CHECK("poly_is_kernel");
-    int nrec = 0;
-    const double *rec =
-        merge_partials_first<kPolyNF>(a.part, blocks, a.part + (size_t)blocks * (4 + kPolyNF), &nrec, st);
-    PPL_LAUNCH_CHECK("partial_merge_kernel");
-    hipLaunchKernelGGL(weights_finalize_kernel<kPolyNF>, dim3(1), dim3(kFinalizeThreads), 0, st, rec, nrec, a.N,
-                       (int)PPL_MODEL_POLY, a.scalars, a.summaries);
-    PPL_LAUNCH_CHECK("weights_finalize_kernel");
-    return PPL_OK;
+    return finalize_weights<kPolyNF>(a.part, blocks, a.part + (size_t)blocks * (4 + kPolyNF), a.N, (int)PPL_MODEL_POLY, a.scalars,
+                                a.summaries, st);
 }
 
 int run_importance(const IsArgs &a, hipStream_t st) {

@@ -27,7 +27,6 @@
 namespace ppl {
 
 constexpr int kPropThreads = 256;
-constexpr int kPolyNFp = 29;
 constexpr int kGmmNF = 8;
 constexpr double kHalfLog2PiD = 0.91893853320467274178;
 
@@ -156,7 +155,7 @@ __global__ __launch_bounds__(kPropThreads) void poly_mix_is_kernel(
             for (int j = 0; j < 5; ++j) lat_out[(size_t)(1 + j) * N + i] = c[j];
         }
     }
-    Partial<kPolyNFp> pp = partial_empty<kPolyNFp>();
+    Partial<kPolyNF> pp = partial_empty<kPolyNF>();
     if (live && isnan(lw)) pp.nan = 1.0;
     pp.m = lw;
     if (lw > -INFINITY) {
@@ -170,12 +169,10 @@ __global__ __launch_bounds__(kPropThreads) void poly_mix_is_kernel(
 #pragma unroll
             for (int j = 0; j < 5; ++j) pp.f[4 + 5 * s + j] = sel * c[j];
         }
-#pragma unroll
-        for (int j = 0; j < 5; ++j) pp.f[24 + j] = c[j];
     } else {
         pp.m = -INFINITY;
     }
-    partial_block_reduce_store<kPolyNFp, kPropThreads / 64>(pp, part + (size_t)blockIdx.x * (4 + kPolyNFp));
+    partial_block_reduce_store<kPolyNF, kPropThreads / 64>(pp, part + (size_t)blockIdx.x * (4 + kPolyNF));
 }
 
 // --------------------------------------------------------------- GMM --
@@ -370,7 +367,7 @@ __global__ __launch_bounds__(kPropThreads) void gmm_is_kernel(const float *__res
 // ---------------------------------------------------------------- host --
 size_t prop_partial_bytes(int model, int64_t N) {
     const int64_t blocks = (N + kPropThreads - 1) / kPropThreads;
-    const int nf = model == PPL_MODEL_POLY ? kPolyNFp : kGmmNF;
+    const int nf = model == PPL_MODEL_POLY ? kPolyNF : kGmmNF;
     return (size_t)blocks * (4 + nf) * sizeof(double) + merge_scratch_bytes(nf);
 }
 
@@ -396,22 +393,11 @@ int run_importance_q(const IsArgs &a, hipStream_t st) {
         timer.stop();
         PPL_LAUNCH_CHECK(name);
     }
-    int nrec = 0;
-    if (a.model == PPL_MODEL_POLY) {
-        const double *rec =
-            merge_partials_first<kPolyNFp>(a.part, blocks, a.part + (size_t)blocks * (4 + kPolyNFp), &nrec, st);
-        PPL_LAUNCH_CHECK("partial_merge_kernel");
-        hipLaunchKernelGGL(weights_finalize_kernel<kPolyNFp>, dim3(1), dim3(kFinalizeThreads), 0, st, rec, nrec, a.N, a.model,
-                           a.scalars, a.summaries);
-    } else {
-        const double *rec =
-            merge_partials_first<kGmmNF>(a.part, blocks, a.part + (size_t)blocks * (4 + kGmmNF), &nrec, st);
-        PPL_LAUNCH_CHECK("partial_merge_kernel");
-        hipLaunchKernelGGL(weights_finalize_kernel<kGmmNF>, dim3(1), dim3(kFinalizeThreads), 0, st, rec, nrec, a.N, a.model,
-                           a.scalars, a.summaries);
-    }
-    PPL_LAUNCH_CHECK("weights_finalize_kernel");
-    return PPL_OK;
+    if (a.model == PPL_MODEL_POLY)
+        return finalize_weights<kPolyNF>(a.part, blocks, a.part + (size_t)blocks * (4 + kPolyNF), a.N, a.model, a.scalars,
+                                         a.summaries, st);
+    return finalize_weights<kGmmNF>(a.part, blocks, a.part + (size_t)blocks * (4 + kGmmNF), a.N, a.model, a.scalars,
+                                    a.summaries, st);
 }
 
 }  // namespace ppl
