@@ -119,7 +119,7 @@ __global__ __launch_bounds__(kMcThreads) void mcmc_poly_kernel(
         }
         const double ll2 = mc_loglik(c2, X, Y, D);
         const double la = (ll2 - ll) + (log_size(n + 1) - log_size(n2 + 1));
-        const bool acc = log((double)unit_f32(w.z)) < la;
+        const bool acc = log_unit((double)unit_f32(w.z)) < la;
         if (valid && la_tr) la_tr[t * C + c] = la;
         if (acc) {
             n = n2;

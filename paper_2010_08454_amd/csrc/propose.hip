@@ -261,7 +261,7 @@ __global__ __launch_bounds__(kPropThreads) void gmm_is_kernel(const float *__res
         double E[8], tot = 0.0;
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
-            E[k] = k < K ? -log(u01d(ew[k])) : 0.0;
+            E[k] = k < K ? -log_unit(u01d(ew[k])) : 0.0;
             if (k < K) tot += E[k];
         }
 #pragma unroll

@@ -309,7 +309,7 @@ __device__ __forceinline__ void simulate_block(const SimSpec &sp, int B, Key key
         double E[8], pi[8], mu[8], z[8], etot = 0.0;
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
-            E[k] = k < K ? -log(u01(ew[k])) : 0.0;
+            E[k] = k < K ? -log_unit(u01(ew[k])) : 0.0;
             if (k < K) etot += E[k];
         }
 #pragma unroll

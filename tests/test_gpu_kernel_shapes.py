@@ -70,3 +70,34 @@ def test_blr_nonfinite_rows(ppl, n, row):
         lw, _, scal = _blr(ppl, Xb, y, n, 3)
         assert scal[3] == status
         assert np.all(np.isneginf(lw)) if value == np.inf else np.all(np.isnan(lw))
+
+
+# ------------------------------------------------------ FP64 Box-Muller --
+@pytest.mark.parametrize("seed", [1, 2 ** 63 + 5])
+def test_poly_draws_64bit(ppl, seed):
+    """Coefficient draws against numpy's extended precision: a pair r cos, r sin
+    carries at most one unit in the last place from each of r (half of the
+    logarithm's), the trigonometric value and the product: 3 x 2^-53 relative."""
+    import torch
+    n = 200_003
+    data = ppl.make_data(torch.zeros(1, dtype=torch.float64, device="cuda"),
+                         torch.zeros(1, dtype=torch.float64, device="cuda"))
+    lat = torch.empty((6, n), dtype=torch.float64, device="cuda")
+    ppl.ppl_importance(ppl.PPL_MODEL_POLY, data, n, seed, latents=lat)
+    lat = lat.cpu().numpy()
+    pi = np.longdouble("3.14159265358979323846264338327950288")
+    for b in (1, 2, 3):
+        w = ppl.ppl_philox(seed, b, 0, 0, n).cpu().numpy().view(np.uint32).astype(np.uint64)
+        u = [(((w[:, 2 * h + 1] << np.uint64(32)) | w[:, 2 * h]) >> np.uint64(12)).astype(np.float64) + 0.5 for h in (0, 1)]
+        u = [np.longdouble(v) * np.longdouble(2.0) ** -52 for v in u]
+        r = np.sqrt(-2 * np.log(u[0]))
+        q = np.rint(4 * u[1])
+        t = pi * (2 * u[1] - q / 2)                    # exact reduction to a quarter turn
+        q = q.astype(int) % 4
+        c, s = np.cos(t), np.sin(t)
+        cs = np.choose(q, [c, -s, -c, s]), np.choose(q, [s, c, -s, -c])
+        for h in (0, 1):
+            j = 2 * (b - 1) + h
+            if j < 5:
+                ref = 10 * r * cs[h]
+                assert np.max(np.abs(lat[1 + j] - ref) / np.abs(ref)) <= 4 * 2.0 ** -53
