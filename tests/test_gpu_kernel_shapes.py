@@ -75,9 +75,9 @@ def test_blr_nonfinite_rows(ppl, n, row):
 # ------------------------------------------------------ FP64 Box-Muller --
 @pytest.mark.parametrize("seed", [1, 2 ** 63 + 5])
 def test_poly_draws_64bit(ppl, seed):
-    """Coefficient draws against numpy's extended precision: a pair r cos, r sin
-    carries at most one unit in the last place from each of r (half of the
-    logarithm's), the trigonometric value and the product: 3 x 2^-53 relative."""
+    """Coefficient draws against numpy's extended precision.  In units of 2^-52
+    relative: half of the logarithm's error 0.5, the root's rounding 0.5, the
+    trigonometric value 1, the products with it and with the prior sd 0.5 each."""
     import torch
     n = 200_003
     data = ppl.make_data(torch.zeros(1, dtype=torch.float64, device="cuda"),
@@ -100,4 +100,4 @@ def test_poly_draws_64bit(ppl, seed):
             j = 2 * (b - 1) + h
             if j < 5:
                 ref = 10 * r * cs[h]
-                assert np.max(np.abs(lat[1 + j] - ref) / np.abs(ref)) <= 4 * 2.0 ** -53
+                assert np.max(np.abs(lat[1 + j] - ref) / np.abs(ref)) <= 3 * 2.0 ** -52
