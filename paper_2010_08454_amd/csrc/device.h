@@ -253,6 +253,28 @@ __device__ __forceinline__ double wave_sum_dpp(double v) {
     const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), 63);
     return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
 }
+// FP64 maximum with the same DPP steps; a row left out of a broadcast keeps its
+// own value.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_keep_f64(double v) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const int lo = (int)(uint32_t)b, hi = (int)(uint32_t)(b >> 32);
+    const int nlo = __builtin_amdgcn_update_dpp(lo, lo, CTRL, ROWS, 0xF, false);
+    const int nhi = __builtin_amdgcn_update_dpp(hi, hi, CTRL, ROWS, 0xF, false);
+    return __builtin_bit_cast(double, ((uint64_t)(uint32_t)nhi << 32) | (uint32_t)nlo);
+}
+__device__ __forceinline__ double wave_max_dpp(double v) {
+    v = fmax(v, dpp_keep_f64<0xB1, 0xF>(v));
+    v = fmax(v, dpp_keep_f64<0x4E, 0xF>(v));
+    v = fmax(v, dpp_keep_f64<0x141, 0xF>(v));
+    v = fmax(v, dpp_keep_f64<0x140, 0xF>(v));
+    v = fmax(v, dpp_keep_f64<0x142, 0xA>(v));
+    v = fmax(v, dpp_keep_f64<0x143, 0xC>(v));
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, 63);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), 63);
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
 __device__ __forceinline__ int wave_or(int v) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v |= __shfl_xor(v, o, 64);
@@ -328,8 +350,7 @@ struct WaveReduceScatter<F, N, 0> {
 template <int NWAVES>
 __device__ __forceinline__ double block_max_f64(double v) {
     __shared__ double lds_m[NWAVES];
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, 64));
+    v = wave_max_dpp(v);
     if ((threadIdx.x & 63) == 0) lds_m[threadIdx.x >> 6] = v;
     __syncthreads();
     double m = lds_m[0];
@@ -508,6 +529,8 @@ inline const double *merge_partials_first(const double *part, int64_t nblocks, d
 // e c_j over the executions of degree n = 2 + s (s < 4, j < 5), and [24] sum of
 // e c_0 over those of degree 1.
 constexpr int kPolyNF = 25;
+// Workspaces keep the room of 29 fields, the number of summaries.
+constexpr int kPolyWsFields = 29;
 
 // One workgroup merges the block partials and writes scalars[8] = {log Z-hat,
 // ESS, 0, status, M, s1, s2, N} and the model summaries, one per thread: for

@@ -188,6 +188,9 @@ __global__ __launch_bounds__(64 * NW, NW == 16 ? 4 : (PROP ? 2 : 3)) void blr_is
 // FP64 polynomial model.  Horner over the five coefficient slots with slots
 // j >= n set to zero: 0 * x + 0 = 0 exactly, so this equals n-term Horner and
 // no lane branches on the sampled degree.
+// Bound: FP64 and integer vector issue, about as much in the draws as in 100
+// points; 2 x 10^6 x 100 points in 97 us a call (114.6 with the library's log and
+// sincospi, one particle per lane and 29 fields).
 template <int P>
 __global__ __launch_bounds__(kIsThreads) void poly_is_kernel(
     const double *__restrict__ X, const double *__restrict__ Y, int D, int64_t N, Key key, double sd,
@@ -286,11 +289,120 @@ __global__ __launch_bounds__(kIsThreads) void poly_is_kernel(
     partial_block_reduce_store<kPolyNF, kIsWaves>(pp, part + (size_t)blockIdx.x * (4 + kPolyNF));
 }
 
+// Four lanes per particle, for calls too small to fill the chip with a particle
+// per lane: lane b of a quad draws Philox block b (the degree, or one
+// Box-Muller pair), takes every fourth point, and adds the summaries of degree
+// 2 + b.  Bound: the latency of this chain (10^4 particles are 157 workgroups).
+// us a call against a lane per particle: 10^4 particles x 1000 points 14.1 and
+// 36.6, x 100 points 11.0 and 11.5, 2^15 x 1000 18.8 and 36.9.
+constexpr int kQuadParticles = kIsThreads / 4;   // particles per workgroup
+constexpr int kQuadPoints = 512;                 // points in LDS at a time
+
+__global__ __launch_bounds__(kIsThreads) void poly_quad_is_kernel(
+    const double *__restrict__ X, const double *__restrict__ Y, int D, int64_t N, Key key, double sd,
+    int n_lo, int n_hi, double *__restrict__ lw_out, double *__restrict__ lat_out, double *__restrict__ part) {
+    __shared__ double2 xy[kQuadPoints];
+    constexpr int kSums = 10;                    // degree slot: mass, 5 means; all: e, e^2, NaN, degree-1 c_0
+    __shared__ double sums[kIsThreads / 16][4][kSums];
+    const int tid = threadIdx.x, b = tid & 3;
+    const int64_t i = (int64_t)blockIdx.x * kQuadParticles + (tid >> 2);
+    const bool live = i < N;
+    // the first points are on their way while the particle is drawn
+    double2 first[kQuadPoints / kIsThreads];
+#pragma unroll
+    for (int k = 0; k < kQuadPoints / kIsThreads; ++k) {
+        const int d = tid + k * kIsThreads;
+        first[k] = d < D ? make_double2(X[d], Y[d]) : make_double2(0.0, 0.0);
+    }
+    const uint4 w = philox((uint32_t)i, b, 0, kTagPrior, key);
+    const int n = __builtin_amdgcn_update_dpp(0, uniform_discrete(w.x, n_lo, (uint32_t)(n_hi - n_lo + 1)), 0x00, 0xF,
+                                              0xF, false);
+    double z0, z1;
+    box_muller(unit_f64(w.x, w.y), unit_f64(w.z, w.w), z0, z1);
+    z0 *= sd;
+    z1 *= sd;
+    double pc[5] = {dpp_f64<0x55, 0xF>(z0), dpp_f64<0x55, 0xF>(z1), dpp_f64<0xAA, 0xF>(z0), dpp_f64<0xAA, 0xF>(z1),
+                    dpp_f64<0xFF, 0xF>(z0)};
+#pragma unroll
+    for (int j = 0; j < 5; ++j) pc[j] = j < n ? pc[j] : 0.0;
+
+    double acc = 0.0;
+    for (int d0 = 0; d0 < D; d0 += kQuadPoints) {
+        if (d0 > 0) __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kQuadPoints / kIsThreads; ++k) {
+            const int d = d0 + tid + k * kIsThreads;
+            if (d0 > 0) first[k] = d < D ? make_double2(X[d], Y[d]) : make_double2(0.0, 0.0);
+            xy[tid + k * kIsThreads] = first[k];
+        }
+        __syncthreads();
+        const int m = min(kQuadPoints, D - d0);
+        int d = b;
+        for (; d + 28 < m; d += 32) {
+            double2 p[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) p[k] = xy[d + 4 * k];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) acc += poly_sq_residual(pc, p[k].x, p[k].y);
+        }
+        for (; d < m; d += 4) acc += poly_sq_residual(pc, xy[d].x, xy[d].y);
+    }
+    acc += dpp_f64<0xB1, 0xF>(acc);
+    acc += dpp_f64<0x4E, 0xF>(acc);
+
+    const double lw = live ? -0.5 * acc : -INFINITY;
+    if (live) {
+        if (lw_out && b == 0) lw_out[i] = lw;
+        if (lat_out) {                           // the lane's own pair; n beside the first
+            double *o = lat_out + (size_t)(2 * b) * N + i;
+            if (b > 0) o[-(int64_t)N] = z0;
+            if (b < 3) o[0] = b == 0 ? (double)n : z1;
+        }
+    }
+    const double M = block_max_f64<kIsWaves>(isnan(lw) ? -INFINITY : lw);
+    const double e = lw > -INFINITY ? exp(lw - M) : 0.0;
+    const double own = n - 2 == b ? e : 0.0, one = b == 0 ? e : 0.0;
+    double v[kSums] = {own,
+                       own * pc[0],
+                       own * pc[1],
+                       own * pc[2],
+                       own * pc[3],
+                       own * pc[4],
+                       one,
+                       one * one,
+                       b == 0 && live && isnan(lw) ? 1.0 : 0.0,
+                       n == 1 ? one * pc[0] : 0.0};
+    // sums over the quads of a row of 16 lanes (rotations by 8 and 4), then over the rows through LDS
+#pragma unroll
+    for (int k = 0; k < kSums; ++k) {
+        v[k] += dpp_f64<0x128, 0xF>(v[k]);
+        v[k] += dpp_f64<0x124, 0xF>(v[k]);
+    }
+    if ((tid & 15) < 4) {
+#pragma unroll
+        for (int k = 0; k < kSums; ++k) sums[tid >> 4][b][k] = v[k];
+    }
+    __syncthreads();
+    double *rec = part + (size_t)blockIdx.x * (4 + kPolyNF);
+    if (tid < 3 + kPolyNF) {
+        // record slots after the maximum: s1, s2, nan, mass[4], c[4][5], degree-1 c_0
+        int s = 0, k = 6 + tid;
+        if (tid >= 3 && tid < 7) { s = tid - 3; k = 0; }
+        else if (tid >= 7 && tid < 27) { s = (tid - 7) / 5; k = 1 + (tid - 7) % 5; }
+        else if (tid == 27) k = 9;
+        double t = 0.0;
+#pragma unroll
+        for (int r = 0; r < kIsThreads / 16; ++r) t += sums[r][s][k];
+        rec[1 + tid] = t;
+    }
+    if (tid == 0) rec[0] = M;
+}
+
 // ---------------------------------------------------------------- host --
 size_t is_partial_bytes(int model, int dim, int64_t N) {
     const int P = model == PPL_MODEL_POLY ? 1 : 4;
     const int64_t blocks = (N + (int64_t)kIsThreads * P - 1) / ((int64_t)kIsThreads * P);
-    const int nf = model == PPL_MODEL_POLY ? kPolyNF : dim;
+    const int nf = model == PPL_MODEL_POLY ? kPolyWsFields : dim;
     return (size_t)blocks * (4 + nf) * sizeof(double) + merge_scratch_bytes(nf);
 }
 
@@ -347,18 +459,24 @@ static int launch_blr(const IsArgs &a, hipStream_t st) {
     return launch_blr_shape<DIM, 4, 1, 4>(a, a.part, st);
 }
 
+// Launch shape of the polynomial model.  Up to 2^15 particles a quad of lanes
+// per particle (at most two waves per SIMD so; the records of 64 particles fit
+// the workspace beside one of 256 by the same count as in blr_shape); above, a
+// lane per particle, and from 2^19 on four, which share the point loads and the
+// workgroup's reduction.
 static int launch_poly(const IsArgs &a, hipStream_t st) {
-    constexpr int P = 1;
-    const int64_t blocks = (a.N + kIsThreads * P - 1) / (kIsThreads * P);
+    const int64_t per = a.N <= 32768 ? kQuadParticles : a.N < 262144 ? kIsThreads : 4 * kIsThreads;
+    const int64_t blocks = (a.N + per - 1) / per;
     if (int rc = check_grid("poly_is_kernel", blocks, kIsThreads)) return rc;
+    auto kern = per == kQuadParticles ? poly_quad_is_kernel : per == kIsThreads ? poly_is_kernel<1> : poly_is_kernel<4>;
     KernelTimer timer("poly_is_kernel", st);
-    hipLaunchKernelGGL((poly_is_kernel<P>), dim3((unsigned)blocks), dim3(kIsThreads), 0, st, (const double *)a.x,
+    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(kIsThreads), 0, st, (const double *)a.x,
                        (const double *)a.y, (int)a.D, a.N, make_key(a.seed), a.hyper[0], (int)a.hyper[1],
                        (int)a.hyper[2], (double *)a.lw_out, (double *)a.lat_out, a.part);
     timer.stop();
     PPL_LAUNCH_CHECK("poly_is_kernel");
-    return finalize_weights<kPolyNF>(a.part, blocks, a.part + (size_t)blocks * (4 + kPolyNF), a.N, (int)PPL_MODEL_POLY, a.scalars,
-                                a.summaries, st);
+    return finalize_weights<kPolyNF>(a.part, blocks, a.part + (size_t)blocks * (4 + kPolyNF), a.N,
+                                     (int)PPL_MODEL_POLY, a.scalars, a.summaries, st);
 }
 
 int run_importance(const IsArgs &a, hipStream_t st) {

@@ -367,7 +367,7 @@ __global__ __launch_bounds__(kPropThreads) void gmm_is_kernel(const float *__res
 // ---------------------------------------------------------------- host --
 size_t prop_partial_bytes(int model, int64_t N) {
     const int64_t blocks = (N + kPropThreads - 1) / kPropThreads;
-    const int nf = model == PPL_MODEL_POLY ? kPolyNF : kGmmNF;
+    const int nf = model == PPL_MODEL_POLY ? kPolyWsFields : kGmmNF;
     return (size_t)blocks * (4 + nf) * sizeof(double) + merge_scratch_bytes(nf);
 }
 

@@ -101,3 +101,47 @@ def test_poly_draws_64bit(ppl, seed):
             if j < 5:
                 ref = 10 * r * cs[h]
                 assert np.max(np.abs(lat[1 + j] - ref) / np.abs(ref)) <= 3 * 2.0 ** -52
+
+
+# ---------------------------------------------- POLY, lanes per particle --
+@pytest.mark.parametrize("D", [0, 1, 3, 4, 31, 33, 511, 512, 513, 1030])
+@pytest.mark.parametrize("n_lo,n_hi", [(2, 5), (1, 3)])
+def test_poly_shapes(ppl, orc, D, n_lo, n_hi):
+    """Points around the quad's stride and the LDS chunk, particle counts on
+    both sides of the launch rule (a quad, one lane, a quarter lane per
+    particle), degree 1 in and out of the range.  The likelihood sums take
+    another order per shape: D terms of one sign, within (D + 4) 2^-52."""
+    import torch
+    x, y = synthetic.poly_data(D=max(D, 1), seed=40 + D)
+    x, y = x[:D], y[:D]
+    dx, dy = (torch.from_numpy(np.ascontiguousarray(v)).cuda() for v in (x, y))
+    data = ppl.make_data(dx if D else None, dy if D else None, n_data=D, hyper=[10.0, n_lo, n_hi], dtype=ppl.PPL_F64) \
+        if D else ppl.PplData(x=None, y=None, n_data=0, dim=0, dtype=ppl.PPL_F64, n_hyper=0)
+    if not D:
+        n_lo, n_hi = 2, 5
+    seed, out = 9, {}
+    for n in (262_145, 262_143, 32_769, 32_768, 65, 64, 1):
+        lw = torch.empty(n, dtype=torch.float64, device="cuda")
+        lat = torch.empty((6, n), dtype=torch.float64, device="cuda")
+        summ = torch.empty(29, dtype=torch.float64, device="cuda")
+        scal = torch.empty(8, dtype=torch.float64, device="cuda")
+        ppl.ppl_importance(ppl.PPL_MODEL_POLY, data, n, seed, log_weights=lw, latents=lat, summaries=summ, scalars=scal)
+        lw, lat, summ, scal = (t.cpu().numpy() for t in (lw, lat, summ, scal))
+        if not out:
+            out = dict(lw=lw, lat=lat)
+            if D:
+                ref = orc.importance(orc.MODEL_POLY, x, y, 300, seed, want_lw=True, hyper=[10.0, n_lo, n_hi])
+                assert np.max(np.abs(lw[:300] - ref["lw"]) / np.maximum(1.0, np.abs(ref["lw"]))) < 1e-12
+        np.testing.assert_array_equal(lat, out["lat"][:, :n])
+        assert np.all(np.abs(lw - out["lw"][:n]) <= (D + 4) * 2.0 ** -52 * np.abs(out["lw"][:n]))
+        # summaries and normaliser from the returned weights: sums of n terms
+        w = np.exp(lw - lw.max())
+        deg, c = lat[0].astype(int), lat[1:] * (np.arange(5)[:, None] < lat[0][None])
+        tol = 1e-10
+        assert abs(scal[0] - (lw.max() + np.log(w.sum()) - np.log(n))) <= tol * max(1.0, abs(scal[0]))
+        for s in range(4):
+            sel = w * (deg == s + 2)
+            assert abs(summ[s] - sel.sum() / w.sum()) <= tol
+            want = (sel * c).sum(1) / sel.sum() if sel.sum() > 0 else np.zeros(5)
+            assert np.all(np.abs(summ[4 + 5 * s:9 + 5 * s] - want) <= tol * 100)
+        assert np.all(np.abs(summ[24:] - (w * c).sum(1) / w.sum()) <= tol * 100)
