@@ -946,15 +946,12 @@ int ppl_proposal_infer(int model, const ppl_data *data, const void *d_weights, i
     hipStream_t st = (hipStream_t)stream;
     char *base = (char *)ws;
     double *scal = (double *)base;
-    const TrainBufs b = train_bufs(base + 256, 64);
     double *q = (double *)(base + 256 + align_up(train_ws_bytes(64), 256));
     double *part = q + 512;
     const MlpView w = mlp_view(const_cast<void *>(d_weights));
-    if (int rc = launch_observed_summary(model, data->x, data->y, data->n_data, b.x_row, d_data_summaries, st)) return rc;
-    if (int rc = launch_forward(w, b, false, st)) return rc;
-    if (int rc = launch_decode(model, data->dim, b.o_col, 64, log(widen), q, st)) return rc;
-    const int nq = model == PPL_MODEL_POLY ? kPolyQParams : gmm_q_params(data->dim);
-    if (d_q_params) PPL_HIP(hipMemcpyAsync(d_q_params, q, (size_t)nq * sizeof(double), hipMemcpyDeviceToDevice, st));
+    if (int rc = launch_infer_net(model, data->dim, data->x, data->y, data->n_data, w, log(widen), q, d_q_params,
+                                  d_data_summaries, st))
+        return rc;
     a.model = model;
     a.x = data->x;
     a.y = data->y;

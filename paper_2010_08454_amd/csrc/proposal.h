@@ -34,11 +34,6 @@ struct SimSpec {
 int launch_simulate(const SimSpec &sp, int B, uint64_t seed, const int64_t *step, uint16_t *x_row, uint16_t *x_col,
                     double *theta, double *s64, hipStream_t st);
 
-// Summaries of one observed dataset into row 0 of x_row[64][64] (rows 1..63
-// cleared) and, if s64 is not null, the FP64 values s64[64].
-int launch_observed_summary(int model, const void *x, const void *y, int64_t D, uint16_t *x_row, double *s64,
-                            hipStream_t st);
-
 // Training-step buffers (device), all allocated from one workspace.
 struct TrainBufs {
     int B;
@@ -99,9 +94,11 @@ int launch_update_simulate(const MlpView &w, const TrainBufs &b, const AdamSpec 
 int launch_set_i64(int64_t *p, int64_t v, hipStream_t st);
 int launch_init_weights(void *weights, uint64_t seed, hipStream_t st);
 
-// Decode the network output column 0 of o_col[256][ld] into FP64 proposal
-// parameters (kPolyQParams or gmm_q_params(K) values); log_widen is added to
-// every used log-scale.
-int launch_decode(int model, int K, const float *o_col, int ld, double log_widen, double *q, hipStream_t st);
+// The proposal network on one observed dataset, in one launch: its summaries
+// (also to s64[64] if not null), the forward pass and the decoded FP64 proposal
+// parameters (kPolyQParams or gmm_q_params(K) values) in q and, if not null,
+// q_copy; log_widen is added to every used log-scale.
+int launch_infer_net(int model, int K, const void *x, const void *y, int64_t D, const MlpView &w, double log_widen,
+                     double *q, double *q_copy, double *s64, hipStream_t st);
 
 }  // namespace ppl

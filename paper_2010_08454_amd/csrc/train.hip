@@ -1,5 +1,5 @@
 // train.hip -- training of the proposal network: mixture-density loss head,
-// backward pass, Adam, weight initialisation and the decoded proposal.
+// backward pass, Adam and weight initialisation.
 //
 // The network (64 -> 256 -> 256 -> 256, ReLU after the first two layers, BF16
 // MFMA products with FP32 accumulation) maps the summaries s(y) of a dataset
@@ -18,6 +18,7 @@
 //         mixture logits, o[8 : 8 + 8d] means (5 o), then 8d log-scales.
 #include "adam.h"
 #include "device.h"
+#include "fuse.h"
 #include "host.h"
 #include "proposal.h"
 #include "timing.h"
@@ -27,8 +28,6 @@ namespace ppl {
 constexpr float kHalfLog2Pi = 0.91893853320467274f;
 constexpr uint32_t kTagInit = 5;
 constexpr int kLdsRow = 258;          // BF16 per LDS row of the head (odd word stride)
-
-__host__ __device__ constexpr int poly_head_off(int n) { return 12 + 8 * (n - 2) * (n + 1); }
 
 // ---------------------------------------------------------------- head --
 // Eight lanes per training pair, lane m owning mixture component m; 32 pairs
@@ -195,52 +194,6 @@ constexpr int kFuseRows = 32;
 constexpr int kFusePad = 264;           // BF16 per LDS row
 constexpr int kFuseOPad = 260;          // FP32 per LDS row of the outputs
 
-typedef __bf16 fbf16x8_t __attribute__((ext_vector_type(8)));
-typedef float ffloatx4_t __attribute__((ext_vector_type(4)));
-
-// A product's weight fragments for this wave: fb[s][j] holds B rows
-// 64 wave + 16 j + lane % 16, K entries 32 s + 8 (lane / 16) .. + 7, read from
-// the fragment-order copy of the weights (frag_index: each load instruction
-// reads 1 KB of consecutive bytes; from the [out][in] or [in][out] layout a
-// wave's load touched 16 rows, 64 bytes of each).  They are loaded one product
-// ahead (while the previous product's epilogue and the workgroup barrier run),
-// so a product waits for global memory at most once.
-typedef fbf16x8_t FuseFrags[8][4];
-
-template <int KD>
-__device__ __forceinline__ void fuse_load_w(const uint16_t *Bw, FuseFrags &fb) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int fr = lane & 15, fk = (lane >> 4) * 8;
-#pragma unroll
-    for (int s = 0; s < KD / 32; ++s)
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            fb[s][j] = *(const fbf16x8_t *)(Bw + frag_index(64 * wave + 16 * j + fr, 32 * s + fk, KD));
-    __builtin_amdgcn_sched_barrier(0);       // keep the scheduler from sinking the loads into the MFMA loop
-}
-
-// acc[i][j][q] = C[16 i + 4 (lane / 16) + q][64 wave + 16 j + lane % 16] of
-// C[32][256] = A[32][KD] B[256][KD]^T, B's fragments in fb.
-template <int KD>
-__device__ __forceinline__ void fuse_mma(const uint16_t *A, int lda, const FuseFrags &fb, ffloatx4_t (&acc)[2][4]) {
-    const int lane = threadIdx.x & 63;
-    const int fr = lane & 15, fk = (lane >> 4) * 8;
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = ffloatx4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int s = 0; s < KD / 32; ++s) {
-        fbf16x8_t fa[2];
-#pragma unroll
-        for (int i = 0; i < 2; ++i) fa[i] = *(const fbf16x8_t *)(A + (size_t)(16 * i + fr) * lda + 32 * s + fk);
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[i], fb[s][j], acc[i][j], 0, 0, 0);
-    }
-}
-
 // Hidden-layer epilogue: relu(acc + bias) in BF16 to LDS rows and to the
 // column-major global copy [256][B] (columns b0 .. b0 + 31).
 __device__ __forceinline__ void fuse_store_hidden(const ffloatx4_t (&acc)[2][4], const float (&bias)[4], uint16_t *lds,
@@ -285,18 +238,6 @@ __device__ __forceinline__ void fuse_store_masked(const ffloatx4_t (&acc)[2][4],
             *(uint2 *)(col + (size_t)n * B + b0 + mb) =
                 make_uint2((uint32_t)h[0] | ((uint32_t)h[1] << 16), (uint32_t)h[2] | ((uint32_t)h[3] << 16));
         }
-}
-
-// Workgroup barrier for data exchanged through LDS only: waits for this
-// wave's LDS operations (lgkmcnt 0) but leaves its global stores and the
-// prefetched weight loads in flight (a full __syncthreads would wait for
-// them at every layer).  Nothing the fused pass stores to global memory is
-// read back by another wave of the workgroup.
-__device__ __forceinline__ void lds_barrier() {
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_waitcnt(0xc07f);      // vmcnt and expcnt: no wait; lgkmcnt: 0
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
 }
 
 template <int MODEL>
@@ -515,43 +456,6 @@ __global__ __launch_bounds__(256) void init_weights_kernel(MlpView w, Key key, f
     w.v[e] = 0.0f;
 }
 
-// -------------------------------------------------------------- decode --
-// FP64 proposal parameters from network output column 0 (log-scales raised
-// by log_widen).
-//   POLY: {log-softmax of the degree logits [4], log-softmax of the mixture
-//          logits [8], mean[4][8][5], lsd[4][8][5]} (slots j >= n zero).
-//   GMM:  {log-softmax of the mixture logits [8], mean[8][d], lsd[8][d]}.
-__global__ __launch_bounds__(64) void decode_kernel(int model, int K, const float *__restrict__ o_col, int ld,
-                                                    double log_widen, double *__restrict__ q) {
-    const int lane = threadIdx.x;
-    auto O = [&](int k) { return (double)o_col[(size_t)k * ld]; };
-    auto logsoftmax = [&](int base, int n, double *dst) {
-        double m = -INFINITY;
-        for (int k = 0; k < n; ++k) m = fmax(m, O(base + k));
-        double s = 0.0;
-        for (int k = 0; k < n; ++k) s += exp(O(base + k) - m);
-        const double ls = log(s);
-        for (int k = 0; k < n; ++k) dst[k] = O(base + k) - m - ls;
-    };
-    if (model == PPL_MODEL_POLY) {
-        if (lane == 0) logsoftmax(0, 4, q);
-        if (lane == 1) logsoftmax(4, 8, q + 4);
-        for (int e = lane; e < 160; e += 64) {
-            const int n = 2 + e / 40, m = (e / 5) % 8, j = e % 5;
-            const int off = poly_head_off(n);
-            q[12 + e] = j < n ? 10.0 * O(off + m * n + j) : 0.0;
-            q[172 + e] = j < n ? 5.0 * tanh(O(off + 8 * n + m * n + j) / 5.0) + log_widen : 0.0;
-        }
-    } else {
-        const int d = 2 * K - 1;
-        if (lane == 0) logsoftmax(0, 8, q);
-        for (int e = lane; e < 8 * d; e += 64) {
-            q[8 + e] = 5.0 * O(8 + e);
-            q[8 + 8 * d + e] = 5.0 * tanh(O(8 + 8 * d + e) / 5.0) + log_widen;
-        }
-    }
-}
-
 // ---------------------------------------------------------------- host --
 static size_t a256(size_t v) { return align_up(v, 256); }
 
@@ -751,12 +655,6 @@ int launch_init_weights(void *weights, uint64_t seed, hipStream_t st) {
     const int blocks = (int)((MlpParams::count() + 255) / 256);
     hipLaunchKernelGGL(init_weights_kernel, dim3(blocks), dim3(256), 0, st, w, make_key(seed), s[0], s[1], s[2]);
     PPL_LAUNCH_CHECK("init_weights_kernel");
-    return PPL_OK;
-}
-
-int launch_decode(int model, int K, const float *o_col, int ld, double log_widen, double *q, hipStream_t st) {
-    hipLaunchKernelGGL(decode_kernel, dim3(1), dim3(64), 0, st, model, K, o_col, ld, log_widen, q);
-    PPL_LAUNCH_CHECK("decode_kernel");
     return PPL_OK;
 }
 
