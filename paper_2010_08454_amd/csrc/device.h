@@ -123,6 +123,30 @@ __device__ __forceinline__ double log_unit(double u) {
     return h + fma((double)k, 0x1.fdf473de6af28p-22, fma(-s, fma(-q, z, f), e));
 }
 
+// exp x for x <= 0 (-inf and NaN included): x = k ln 2 + r with |r| <= ln 2 / 2,
+// exp r = 1 + r + r^2 q(r) (degree 12 in r, interpolated at Chebyshev nodes,
+// error 4e-19), scaled by 2^k; e is the rounding error of r.  27 vector
+// instructions against 42 of the library's exp, which also covers overflow;
+// largest error 0.83 units in the last place (the library's: 0.86).
+__device__ __forceinline__ double exp_le0(double x) {
+    x = x < -800.0 ? -800.0 : x;         // NaN stays
+    const double k = __builtin_rint(x * 0x1.71547652b82fep+0);
+    const double a = fma(k, -0x1.62e42p-1, x);                     // exact
+    const double r = fma(k, -0x1.fdf473de6af28p-22, a), e = fma(k, -0x1.fdf473de6af28p-22, a - r);
+    double q = 0x1.1f730a202ec17p-29;
+    q = fma(q, r, 0x1.af4df5750ec30p-26);
+    q = fma(q, r, 0x1.27e4db6121beep-22);
+    q = fma(q, r, 0x1.71de022bd5558p-19);
+    q = fma(q, r, 0x1.a01a01a6d9931p-16);
+    q = fma(q, r, 0x1.a01a01abe9ce8p-13);
+    q = fma(q, r, 0x1.6c16c16c162d2p-10);
+    q = fma(q, r, 0x1.11111111100d8p-7);
+    q = fma(q, r, 0x1.5555555555556p-5);
+    q = fma(q, r, 0x1.5555555555557p-3);
+    q = fma(q, r, 0x1.0000000000000p-1);
+    return __builtin_ldexp(1.0 + (r + fma(r * r, q, e)), (int)k);
+}
+
 // sqrt x for x in [2^-53, 74]: the reciprocal root estimate refined twice, then
 // one correction of the root itself.
 __device__ __forceinline__ double sqrt_unit(double x) {

@@ -296,24 +296,17 @@ __global__ __launch_bounds__(kIsThreads) void poly_is_kernel(
 // us a call against a lane per particle: 10^4 particles x 1000 points 14.1 and
 // 36.6, x 100 points 11.0 and 11.5, 2^15 x 1000 18.8 and 36.9.
 constexpr int kQuadParticles = kIsThreads / 4;   // particles per workgroup
-constexpr int kQuadPoints = 512;                 // points in LDS at a time
 
 __global__ __launch_bounds__(kIsThreads) void poly_quad_is_kernel(
     const double *__restrict__ X, const double *__restrict__ Y, int D, int64_t N, Key key, double sd,
     int n_lo, int n_hi, double *__restrict__ lw_out, double *__restrict__ lat_out, double *__restrict__ part) {
-    __shared__ double2 xy[kQuadPoints];
-    constexpr int kSums = 10;                    // degree slot: mass, 5 means; all: e, e^2, NaN, degree-1 c_0
-    __shared__ double sums[kIsThreads / 16][4][kSums];
+    __shared__ double2 xy[kGroupPoints];
     const int tid = threadIdx.x, b = tid & 3;
     const int64_t i = (int64_t)blockIdx.x * kQuadParticles + (tid >> 2);
     const bool live = i < N;
     // the first points are on their way while the particle is drawn
-    double2 first[kQuadPoints / kIsThreads];
-#pragma unroll
-    for (int k = 0; k < kQuadPoints / kIsThreads; ++k) {
-        const int d = tid + k * kIsThreads;
-        first[k] = d < D ? make_double2(X[d], Y[d]) : make_double2(0.0, 0.0);
-    }
+    double2 first[kGroupPoints / kIsThreads];
+    poly_group_load<kIsThreads>(X, Y, D, 0, first);
     const uint4 w = philox((uint32_t)i, b, 0, kTagPrior, key);
     const int n = __builtin_amdgcn_update_dpp(0, uniform_discrete(w.x, n_lo, (uint32_t)(n_hi - n_lo + 1)), 0x00, 0xF,
                                               0xF, false);
@@ -326,27 +319,7 @@ __global__ __launch_bounds__(kIsThreads) void poly_quad_is_kernel(
 #pragma unroll
     for (int j = 0; j < 5; ++j) pc[j] = j < n ? pc[j] : 0.0;
 
-    double acc = 0.0;
-    for (int d0 = 0; d0 < D; d0 += kQuadPoints) {
-        if (d0 > 0) __syncthreads();
-#pragma unroll
-        for (int k = 0; k < kQuadPoints / kIsThreads; ++k) {
-            const int d = d0 + tid + k * kIsThreads;
-            if (d0 > 0) first[k] = d < D ? make_double2(X[d], Y[d]) : make_double2(0.0, 0.0);
-            xy[tid + k * kIsThreads] = first[k];
-        }
-        __syncthreads();
-        const int m = min(kQuadPoints, D - d0);
-        int d = b;
-        for (; d + 28 < m; d += 32) {
-            double2 p[8];
-#pragma unroll
-            for (int k = 0; k < 8; ++k) p[k] = xy[d + 4 * k];
-#pragma unroll
-            for (int k = 0; k < 8; ++k) acc += poly_sq_residual(pc, p[k].x, p[k].y);
-        }
-        for (; d < m; d += 4) acc += poly_sq_residual(pc, xy[d].x, xy[d].y);
-    }
+    double acc = poly_group_sq<4, kIsThreads>(pc, X, Y, D, first, xy);
     acc += dpp_f64<0xB1, 0xF>(acc);
     acc += dpp_f64<0x4E, 0xF>(acc);
 
@@ -359,43 +332,7 @@ __global__ __launch_bounds__(kIsThreads) void poly_quad_is_kernel(
             if (b < 3) o[0] = b == 0 ? (double)n : z1;
         }
     }
-    const double M = block_max_f64<kIsWaves>(isnan(lw) ? -INFINITY : lw);
-    const double e = lw > -INFINITY ? exp(lw - M) : 0.0;
-    const double own = n - 2 == b ? e : 0.0, one = b == 0 ? e : 0.0;
-    double v[kSums] = {own,
-                       own * pc[0],
-                       own * pc[1],
-                       own * pc[2],
-                       own * pc[3],
-                       own * pc[4],
-                       one,
-                       one * one,
-                       b == 0 && live && isnan(lw) ? 1.0 : 0.0,
-                       n == 1 ? one * pc[0] : 0.0};
-    // sums over the quads of a row of 16 lanes (rotations by 8 and 4), then over the rows through LDS
-#pragma unroll
-    for (int k = 0; k < kSums; ++k) {
-        v[k] += dpp_f64<0x128, 0xF>(v[k]);
-        v[k] += dpp_f64<0x124, 0xF>(v[k]);
-    }
-    if ((tid & 15) < 4) {
-#pragma unroll
-        for (int k = 0; k < kSums; ++k) sums[tid >> 4][b][k] = v[k];
-    }
-    __syncthreads();
-    double *rec = part + (size_t)blockIdx.x * (4 + kPolyNF);
-    if (tid < 3 + kPolyNF) {
-        // record slots after the maximum: s1, s2, nan, mass[4], c[4][5], degree-1 c_0
-        int s = 0, k = 6 + tid;
-        if (tid >= 3 && tid < 7) { s = tid - 3; k = 0; }
-        else if (tid >= 7 && tid < 27) { s = (tid - 7) / 5; k = 1 + (tid - 7) % 5; }
-        else if (tid == 27) k = 9;
-        double t = 0.0;
-#pragma unroll
-        for (int r = 0; r < kIsThreads / 16; ++r) t += sums[r][s][k];
-        rec[1 + tid] = t;
-    }
-    if (tid == 0) rec[0] = M;
+    poly_group_record<4, kIsWaves>(lw, live, n, pc, part);
 }
 
 // ---------------------------------------------------------------- host --

@@ -21,6 +21,7 @@
 #include "device.h"
 #include "host.h"
 #include "kernels.h"
+#include "poly.h"
 #include "proposal.h"
 #include "timing.h"
 
@@ -54,19 +55,19 @@ __device__ __forceinline__ void stage_scales(const double *__restrict__ lsdv, in
     __syncthreads();
 }
 
-template <int KMAX>
-__device__ __forceinline__ int categorical_exp(double u, const double *__restrict__ logp, int K) {
+// The first k whose running sum of probabilities exceeds u (K - 1 if none);
+// p[k] = exp(logp[k]), formed once per workgroup.
+template <int K>
+__device__ __forceinline__ int categorical_cdf(double u, const double *p) {
     double c = 0.0;
     int r = K - 1;
     bool found = false;
 #pragma unroll
-    for (int k = 0; k < KMAX; ++k) {
-        if (k < K && !found) {
-            c += exp(logp[k]);
-            if (u < c) {
-                r = k;
-                found = true;
-            }
+    for (int k = 0; k < K; ++k) {
+        c += p[k];
+        if (!found && u < c) {
+            r = k;
+            found = true;
         }
     }
     return r;
@@ -74,23 +75,23 @@ __device__ __forceinline__ int categorical_exp(double u, const double *__restric
 
 // -------------------------------------------------------------- POLY --
 __global__ __launch_bounds__(kPropThreads) void poly_mix_is_kernel(
-    const double *__restrict__ X, const double *__restrict__ Y, int D, int64_t N, Key key, double sd,
+    const double *__restrict__ X, const double *__restrict__ Y, int D, int64_t N, Key key, double lsd0, double isd0,
     const double *__restrict__ q, double *__restrict__ lw_out, double *__restrict__ lat_out, double *__restrict__ part) {
     const int64_t i = (int64_t)blockIdx.x * kPropThreads + threadIdx.x;
     const bool live = i < N;
     const uint32_t ii = (uint32_t)i;
     const double *lnl = q, *lmix = q + 4, *mean = q + 12, *lsdv = q + 172;
-    __shared__ double sdv[160], isdv[160];
+    __shared__ double sdv[160], isdv[160], prob[12];
+    if (threadIdx.x < 12) prob[threadIdx.x] = exp(q[threadIdx.x]);
     stage_scales(lsdv, 160, sdv, isdv);
     const uint4 w0 = philox(ii, 0, 0, kTagProposal, key);
-    const int n = 2 + categorical_exp<4>(u01d(w0.x), lnl, 4);
-    const int comp = categorical_exp<8>(u01d(w0.y), lmix, 8);
+    const int n = 2 + categorical_cdf<4>(u01d(w0.x), prob);
+    const int comp = categorical_cdf<8>(u01d(w0.y), prob + 4);
     double z[8];
     normals4_d(philox(ii, 1, 0, kTagProposal, key), z);
     normals4_d(philox(ii, 2, 0, kTagProposal, key), z + 4);
     double c[5];
     double lp = -log(4.0);
-    const double lsd0 = log(sd), isd0 = exp(-lsd0);
 #pragma unroll
     for (int j = 0; j < 5; ++j) {
         const int o = ((n - 2) * 8 + comp) * 5 + j;
@@ -112,7 +113,7 @@ __global__ __launch_bounds__(kPropThreads) void poly_mix_is_kernel(
     }
     double ts = 0.0;
 #pragma unroll
-    for (int m = 0; m < 8; ++m) ts += exp(t[m] - tm);
+    for (int m = 0; m < 8; ++m) ts += exp_le0(t[m] - tm);
     const double lq = lnl[n - 2] + tm + log(ts);
     // Points in chunks of eight (one batch of scalar loads per chunk); the
     // sum order is unchanged.
@@ -175,32 +176,100 @@ __global__ __launch_bounds__(kPropThreads) void poly_mix_is_kernel(
     partial_block_reduce_store<kPolyNF, kPropThreads / 64>(pp, part + (size_t)blockIdx.x * (4 + kPolyNF));
 }
 
+// Eight lanes per particle, for calls too small to fill the chip: lane b draws
+// one Box-Muller pair (b < 3), owns mixture component b of log q and takes every
+// eighth point.  Bound: the latency of the chain.  us a call against a lane per
+// particle: 4096 x 1000 points 23.8 and 52.4, 2^14 x 1000 28.2 and 51.6, 1000 x 50
+// 20.0 and 25.0.
+constexpr int kMixParticles = kPropThreads / 8;      // particles per workgroup
+
+__global__ __launch_bounds__(kPropThreads) void poly_mix_group_is_kernel(
+    const double *__restrict__ X, const double *__restrict__ Y, int D, int64_t N, Key key, double lsd0, double isd0,
+    const double *__restrict__ q, double *__restrict__ lw_out, double *__restrict__ lat_out, double *__restrict__ part) {
+    __shared__ double sdv[160], isdv[160], prob[12];
+    __shared__ double2 xy[kGroupPoints];
+    const int tid = threadIdx.x, b = tid & 7;
+    const int64_t i = (int64_t)blockIdx.x * kMixParticles + (tid >> 3);
+    const bool live = i < N;
+    const uint32_t ii = (uint32_t)i;
+    double2 first[kGroupPoints / kPropThreads];
+    poly_group_load<kPropThreads>(X, Y, D, 0, first);
+    const double *lnl = q, *lmix = q + 4, *mean = q + 12, *lsdv = q + 172;
+    if (tid >= 192 && tid < 204) prob[tid - 192] = exp(q[tid - 192]);
+    stage_scales(lsdv, 160, sdv, isdv);
+    const uint4 w0 = philox(ii, 0, 0, kTagProposal, key);
+    const int n = 2 + categorical_cdf<4>(u01d(w0.x), prob);
+    const int comp = categorical_cdf<8>(u01d(w0.y), prob + 4);
+    const uint4 w = philox(ii, 1 + ((b >> 1) & 1), 0, kTagProposal, key);
+    double za, zb;
+    box_muller(u01d((b & 1) ? w.z : w.x), u01d((b & 1) ? w.w : w.y), za, zb);
+    const double z[5] = {__shfl(za, 0, 8), __shfl(zb, 0, 8), __shfl(za, 1, 8), __shfl(zb, 1, 8), __shfl(za, 2, 8)};
+    double c[5];
+    double lp = -log(4.0), t = lmix[b];
+#pragma unroll
+    for (int j = 0; j < 5; ++j) {
+        const int o = ((n - 2) * 8 + comp) * 5 + j, ob = ((n - 2) * 8 + b) * 5 + j;
+        c[j] = j < n ? mean[o] + sdv[o] * z[j] : 0.0;
+        if (j < n) {
+            lp += log_normal(c[j], 0.0, lsd0, isd0);
+            t += log_normal(c[j], mean[ob], lsdv[ob], isdv[ob]);
+        }
+    }
+    // log q(n, c): degree term plus the mixture over the components, one per lane
+    double tm = fmax(t, dpp_keep_f64<0xB1, 0xF>(t));
+    tm = fmax(tm, dpp_keep_f64<0x4E, 0xF>(tm));
+    tm = fmax(tm, dpp_keep_f64<0x141, 0xF>(tm));
+    double ts = exp_le0(t - tm);
+    ts += dpp_f64<0xB1, 0xF>(ts);
+    ts += dpp_f64<0x4E, 0xF>(ts);
+    ts += dpp_f64<0x141, 0xF>(ts);
+    const double lq = lnl[n - 2] + tm + log(ts);
+    double acc = poly_group_sq<8, kPropThreads>(c, X, Y, D, first, xy);
+    acc += dpp_f64<0xB1, 0xF>(acc);
+    acc += dpp_f64<0x4E, 0xF>(acc);
+    acc += dpp_f64<0x141, 0xF>(acc);
+    const double lw = live ? lp - 0.5 * acc - lq : -INFINITY;
+    if (live) {
+        if (lw_out && b == 6) lw_out[i] = lw;
+        if (lat_out && b < 6) {
+            double v = (double)n;
+#pragma unroll
+            for (int j = 0; j < 5; ++j) v = b == j + 1 ? c[j] : v;
+            lat_out[(size_t)b * N + i] = v;
+        }
+    }
+    poly_group_record<8, kPropThreads / 64>(lw, live, n, c, part);
+}
+
 // --------------------------------------------------------------- GMM --
 // One datum's log-factor, log sum_k pi_k Normal(y; mu_k, sd), in FP32 with the
 // max shift and the hardware exp and log, as in the batched mixture SMC;
-// c[k] = log pi_k - log(sd sqrt(2 pi)).  KK components, fully unrolled.
+// hc[k] = (log pi_k - log(sd sqrt(2 pi))) / 2, hisd = 1 / (2 sd).  The terms are
+// kept halved: t / 2 = c / 2 - (r / 2)^2 takes one instruction fewer than
+// t = c - r^2 / 2 and, all scalings being powers of two, the same roundings.
+// KK components, fully unrolled.
 template <int KK>
-__device__ __forceinline__ float gmm_point(float y, const float (&c)[8], const float (&mu)[8], float inv_sd) {
+__device__ __forceinline__ float gmm_point(float y, const float (&hc)[KK], const float (&mu)[KK], float hisd) {
     float t[KK];
 #pragma unroll
     for (int k = 0; k < KK; ++k) {
-        const float r = (y - mu[k]) * inv_sd;
-        t[k] = fmaf(-0.5f * r, r, c[k]);
+        const float h = (y - mu[k]) * hisd;
+        t[k] = fmaf(-h, h, hc[k]);
     }
     float mx = t[0];
 #pragma unroll
     for (int k = 1; k < KK; ++k) mx = fmaxf(mx, t[k]);
     float s = 0.0f;
 #pragma unroll
-    for (int k = 0; k < KK; ++k) s += __expf(t[k] - mx);
-    return mx + __logf(s);
+    for (int k = 0; k < KK; ++k) s += __builtin_amdgcn_exp2f((t[k] - mx) * 0x1.715476p+1f);   // 2 log2 e
+    return fmaf(2.0f, mx, __logf(s));
 }
 
 // Sum of the log-factors over the data: FP32 within blocks of 16 points (one
 // batch of scalar loads each), FP64 across blocks.
 template <int KK>
-__device__ __forceinline__ double gmm_loglik(const float *__restrict__ Y, int D, const float (&c)[8],
-                                             const float (&mu)[8], float isd) {
+__device__ __forceinline__ double gmm_loglik(const float *__restrict__ Y, int D, const float (&hc)[KK],
+                                             const float (&mu)[KK], float hisd) {
     double ll = 0.0;
     int d = 0;
     for (; d + 16 <= D; d += 16) {
@@ -209,148 +278,133 @@ __device__ __forceinline__ double gmm_loglik(const float *__restrict__ Y, int D,
         for (int k = 0; k < 16; ++k) ys[k] = Y[d + k];
         float sb = 0.0f;
 #pragma unroll 4
-        for (int k = 0; k < 16; ++k) sb += gmm_point<KK>(ys[k], c, mu, isd);
+        for (int k = 0; k < 16; ++k) sb += gmm_point<KK>(ys[k], hc, mu, hisd);
         ll += (double)sb;
     }
     if (d < D) {
         float sb = 0.0f;
-        for (; d < D; ++d) sb += gmm_point<KK>(Y[d], c, mu, isd);
+        for (; d < D; ++d) sb += gmm_point<KK>(Y[d], hc, mu, hisd);
         ll += (double)sb;
     }
     return ll;
 }
 
-// The likelihood for the run's component count K (the same for every thread).
-__device__ __forceinline__ double gmm_loglik_k(const float *__restrict__ Y, int D, int K, const double (&lpi)[8],
-                                               const double (&mu)[8], double inv_sd, double cst) {
-    float c[8], muf[8];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-        c[k] = k < K ? (float)(lpi[k] + cst) : 0.0f;
-        muf[k] = k < K ? (float)mu[k] : 0.0f;
-    }
-    const float isd = (float)inv_sd;
-    switch (K) {
-        case 1: return gmm_loglik<1>(Y, D, c, muf, isd);
-        case 2: return gmm_loglik<2>(Y, D, c, muf, isd);
-        case 3: return gmm_loglik<3>(Y, D, c, muf, isd);
-        case 4: return gmm_loglik<4>(Y, D, c, muf, isd);
-        case 5: return gmm_loglik<5>(Y, D, c, muf, isd);
-        case 6: return gmm_loglik<6>(Y, D, c, muf, isd);
-        case 7: return gmm_loglik<7>(Y, D, c, muf, isd);
-        default: return gmm_loglik<8>(Y, D, c, muf, isd);
-    }
-}
+// Model constants, formed on the host: log((K-1)!) + log(K!), log mu_sd,
+// 1 / mu_sd, -log(sd sqrt(2 pi)).
+struct GmmConst {
+    double mu_sd, lfact, lmu, imu, cst;
+    float hisd;
+};
 
-template <bool PROP>
-__global__ __launch_bounds__(kPropThreads) void gmm_is_kernel(const float *__restrict__ Y, int D, int K, int64_t N,
-                                                              Key key, double mu_sd, double comp_sd,
+// K components: a kernel per K, so that the latents, their densities and the
+// sort unroll to exactly K (2 K - 1) slots and only the Box-Muller pairs that are
+// used are drawn.  Bound: vector issue, the FP32 likelihood (100 points of 5
+// components: 3900 slots with the hardware exp and log at half rate) ahead of
+// the FP64 draw and densities (about 2000).  2^20 particles x 100 points, K = 5:
+// 193 us a call against 249 with one kernel for all K, whose densities also took
+// two lgamma, the model's logs and eight exps of the mixture weights per particle.
+template <bool PROP, int K>
+__global__ __launch_bounds__(kPropThreads) void gmm_is_kernel(const float *__restrict__ Y, int D, int64_t N,
+                                                              Key key, GmmConst g,
                                                               const double *__restrict__ q, double *__restrict__ lw_out,
                                                               double *__restrict__ lat_out, double *__restrict__ part) {
     const int64_t i = (int64_t)blockIdx.x * kPropThreads + threadIdx.x;
     const bool live = i < N;
     const uint32_t ii = (uint32_t)i;
-    double lpi[8], mu[8], extra = 0.0;
-    __shared__ double sdv[PROP ? 8 * 15 : 1], isdv[PROP ? 8 * 15 : 1];
-    if constexpr (PROP) stage_scales(q + 8 + 8 * (2 * K - 1), 8 * (2 * K - 1), sdv, isdv);
+    constexpr int d = 2 * K - 1;
+    double lpi[K], mu[K], extra = 0.0;
+    __shared__ double sdv[PROP ? 8 * d : 1], isdv[PROP ? 8 * d : 1], prob[8];
+    if constexpr (PROP) {
+        if (threadIdx.x < 8) prob[threadIdx.x] = exp(q[threadIdx.x]);
+        stage_scales(q + 8 + 8 * d, 8 * d, sdv, isdv);
+    }
     if constexpr (!PROP) {
         // Prior draws (the SMC initial particles): Dirichlet(1) weights as
         // normalised Exp(1) draws, means mu_sd z.
-        const uint4 wa = philox(ii, 0, 0, kTagPrior, key), wb = philox(ii, 1, 0, kTagPrior, key);
-        const uint32_t ew[8] = {wa.x, wa.y, wa.z, wa.w, wb.x, wb.y, wb.z, wb.w};
-        double E[8], tot = 0.0;
+        double E[K], tot = 0.0, z[(K + 3) / 4 * 4];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            E[k] = k < K ? -log_unit(u01d(ew[k])) : 0.0;
-            if (k < K) tot += E[k];
+        for (int b = 0; b < (K + 3) / 4; ++b) {
+            const uint4 we = philox(ii, b, 0, kTagPrior, key);
+            const uint32_t ew[4] = {we.x, we.y, we.z, we.w};
+#pragma unroll
+            for (int k = 4 * b; k < 4 * b + 4; ++k) {
+                if (k < K) {
+                    E[k] = -log_unit(u01d(ew[k - 4 * b]));
+                    tot += E[k];
+                }
+            }
+            normals4_d(philox(ii, 2 + b, 0, kTagPrior, key), z + 4 * b);
         }
 #pragma unroll
-        for (int k = 0; k < 8; ++k) lpi[k] = k < K ? log(E[k] / tot) : -INFINITY;
-        double z[8];
-        normals4_d(philox(ii, 2, 0, kTagPrior, key), z);
-        normals4_d(philox(ii, 3, 0, kTagPrior, key), z + 4);
-#pragma unroll
-        for (int k = 0; k < 8; ++k) mu[k] = mu_sd * z[k];
+        for (int k = 0; k < K; ++k) {
+            lpi[k] = log(E[k] / tot);
+            mu[k] = g.mu_sd * z[k];
+        }
     } else {
-        const int d = 2 * K - 1;
         const double *lmix = q, *mean = q + 8, *lsdv = q + 8 + 8 * d;
         const uint4 w0 = philox(ii, 0, 0, kTagProposal, key);
-        const int comp = categorical_exp<8>(u01d(w0.x), lmix, 8);
-        double z[16], u[15];
-        normals4_d(philox(ii, 1, 0, kTagProposal, key), z);
-        normals4_d(philox(ii, 2, 0, kTagProposal, key), z + 4);
-        normals4_d(philox(ii, 3, 0, kTagProposal, key), z + 8);
-        normals4_d(philox(ii, 4, 0, kTagProposal, key), z + 12);
+        const int comp = categorical_cdf<8>(u01d(w0.x), prob);
+        double z[(d + 3) / 4 * 4], u[d];
 #pragma unroll
-        for (int k = 0; k < 15; ++k) u[k] = k < d ? mean[comp * d + k] + sdv[comp * d + k] * z[k] : 0.0;
+        for (int b = 0; b < (d + 3) / 4; ++b) normals4_d(philox(ii, 1 + b, 0, kTagProposal, key), z + 4 * b);
+#pragma unroll
+        for (int k = 0; k < d; ++k) u[k] = mean[comp * d + k] + sdv[comp * d + k] * z[k];
         // prior density of u and the map to (log pi, mu)
-        double lg[8], lgm = -INFINITY;
+        double lgm = 0.0, lgs = 0.0;
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            lg[k] = k < K - 1 ? u[K + k < 15 ? K + k : 14] : 0.0;
-            if (k < K) lgm = fmax(lgm, lg[k]);
-        }
-        double lgs = 0.0;
+        for (int k = 0; k < K - 1; ++k) lgm = fmax(lgm, u[K + k]);
 #pragma unroll
-        for (int k = 0; k < 8; ++k)
-            if (k < K) lgs += exp(lg[k] - lgm);
+        for (int k = 0; k < K - 1; ++k) lgs += exp_le0(u[K + k] - lgm);
+        lgs += exp_le0(-lgm);
         const double lz = lgm + log(lgs);
-        double lp = lgamma((double)K) + lgamma((double)K + 1.0);
-        const double lmu = log(mu_sd), imu = exp(-lmu);
-        double prev = 0.0;
+        double lp = g.lfact;
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            if (k < K) {
-                mu[k] = k == 0 ? u[0] : prev + exp(u[k]);
-                prev = mu[k];
-                lpi[k] = lg[k] - lz;
-                lp += log_normal(mu[k], 0.0, lmu, imu) + lpi[k];
-                if (k >= 1) lp += u[k];
-            } else {
-                mu[k] = 0.0;
-                lpi[k] = -INFINITY;
-            }
+        for (int k = 0; k < K; ++k) {
+            mu[k] = k == 0 ? u[0] : mu[k > 0 ? k - 1 : 0] + exp(u[k]);
+            lpi[k] = (k < K - 1 ? u[K + k < d ? K + k : 0] : 0.0) - lz;
+            lp += log_normal(mu[k], 0.0, g.lmu, g.imu) + lpi[k];
+            if (k >= 1) lp += u[k];
         }
-        // log q(u)
-        double t[8], tm = -INFINITY;
-#pragma unroll
+        // log q(u): a running log-sum-exp over the components, not unrolled (the
+        // proposal's 16 d scalars at once would spill)
+        double tm = -1e300, ts = 0.0;
+#pragma unroll 1
         for (int m = 0; m < 8; ++m) {
             double a = lmix[m];
-            for (int k = 0; k < d; ++k) a += log_normal(u[k], mean[m * d + k], lsdv[m * d + k], isdv[m * d + k]);
-            t[m] = a;
-            tm = fmax(tm, a);
-        }
-        double ts = 0.0;
 #pragma unroll
-        for (int m = 0; m < 8; ++m) ts += exp(t[m] - tm);
-        extra = lp - (tm + log(ts));
+            for (int k = 0; k < d; ++k) a += log_normal(u[k], mean[m * d + k], lsdv[m * d + k], isdv[m * d + k]);
+            const double e = exp_le0(-fabs(a - tm));
+            ts = a > tm ? fma(ts, e, 1.0) : ts + e;
+            tm = a > tm ? a : tm;
+        }
+        extra = lp - (ts > 0.0 ? tm + log(ts) : NAN);
     }
-    const double cst = -kHalfLog2PiD - log(comp_sd);
-    const double ll = gmm_loglik_k(Y, D, K, lpi, mu, 1.0 / comp_sd, cst);
+    float hc[K], muf[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        hc[k] = 0.5f * (float)(lpi[k] + g.cst);
+        muf[k] = (float)mu[k];
+    }
+    const double ll = gmm_loglik<K>(Y, D, hc, muf, g.hisd);
     const double lw = live ? ll + extra : -INFINITY;
     if (live) {
         if (lw_out) lw_out[i] = lw;
         if (lat_out) {
 #pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                if (k < K) {
-                    lat_out[(size_t)k * N + i] = lpi[k];
-                    lat_out[(size_t)(K + k) * N + i] = mu[k];
-                }
+            for (int k = 0; k < K; ++k) {
+                lat_out[(size_t)k * N + i] = lpi[k];
+                lat_out[(size_t)(K + k) * N + i] = mu[k];
             }
         }
     }
     // summaries: E[mu_(k)] over the means in increasing order
-    double srt[8];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) srt[k] = k < K ? mu[k] : INFINITY;
-#pragma unroll
-    for (int a = 1; a < 8; ++a)
+    for (int a = 1; a < K; ++a)
 #pragma unroll
         for (int b = a; b > 0; --b) {
-            const double lo = fmin(srt[b - 1], srt[b]), hi = fmax(srt[b - 1], srt[b]);
-            srt[b - 1] = lo;
-            srt[b] = hi;
+            const double lo = fmin(mu[b - 1], mu[b]), hi = fmax(mu[b - 1], mu[b]);
+            mu[b - 1] = lo;
+            mu[b] = hi;
         }
     Partial<kGmmNF> pp = partial_empty<kGmmNF>();
     if (live && isnan(lw)) pp.nan = 1.0;
@@ -359,7 +413,7 @@ __global__ __launch_bounds__(kPropThreads) void gmm_is_kernel(const float *__res
         pp.s1 = 1.0;
         pp.s2 = 1.0;
 #pragma unroll
-        for (int k = 0; k < 8; ++k) pp.f[k] = k < K ? srt[k] : 0.0;
+        for (int k = 0; k < K; ++k) pp.f[k] = mu[k];
     }
     partial_block_reduce_store<kGmmNF, kPropThreads / 64>(pp, part + (size_t)blockIdx.x * (4 + kGmmNF));
 }
@@ -371,24 +425,49 @@ size_t prop_partial_bytes(int model, int64_t N) {
     return (size_t)blocks * (4 + nf) * sizeof(double) + merge_scratch_bytes(nf);
 }
 
+template <int K>
+static void launch_gmm_is(const IsArgs &a, int64_t blocks, const GmmConst &g, hipStream_t st) {
+    auto kern = a.q_params ? gmm_is_kernel<true, K> : gmm_is_kernel<false, K>;
+    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(kPropThreads), 0, st, (const float *)a.y, (int)a.D, a.N,
+                       make_key(a.seed), g, (const double *)a.q_params, (double *)a.lw_out, (double *)a.lat_out, a.part);
+}
+
+// Up to 2^14 particles (two waves per SIMD so) the polynomial model takes eight
+// lanes per particle; the records of 32 particles fit the workspace beside one
+// of 256, since up to kMergeDirect records the second merge level's room is free.
 int run_importance_q(const IsArgs &a, hipStream_t st) {
-    const int64_t blocks = (a.N + kPropThreads - 1) / kPropThreads;
+    const bool group = a.model == PPL_MODEL_POLY && a.N <= 16384;
+    const int64_t per = group ? kMixParticles : kPropThreads;
+    const int64_t blocks = (a.N + per - 1) / per;
     const char *name = a.model == PPL_MODEL_POLY ? "poly_mix_is_kernel" : (a.q_params ? "gmm_mix_is_kernel" : "gmm_is_kernel");
     if (int rc = check_grid(name, blocks, kPropThreads)) return rc;
     {
         KernelTimer timer(name, st);
         if (a.model == PPL_MODEL_POLY) {
-            hipLaunchKernelGGL(poly_mix_is_kernel, dim3((unsigned)blocks), dim3(kPropThreads), 0, st,
-                               (const double *)a.x, (const double *)a.y, (int)a.D, a.N, make_key(a.seed), a.hyper[0],
-                               (const double *)a.q_params, (double *)a.lw_out, (double *)a.lat_out, a.part);
-        } else if (a.q_params) {
-            hipLaunchKernelGGL(gmm_is_kernel<true>, dim3((unsigned)blocks), dim3(kPropThreads), 0, st,
-                               (const float *)a.y, (int)a.D, a.dim, a.N, make_key(a.seed), a.hyper[0], a.hyper[1],
-                               (const double *)a.q_params, (double *)a.lw_out, (double *)a.lat_out, a.part);
+            const double lsd0 = log(a.hyper[0]);
+            hipLaunchKernelGGL(group ? poly_mix_group_is_kernel : poly_mix_is_kernel, dim3((unsigned)blocks), dim3(kPropThreads), 0, st,
+                               (const double *)a.x, (const double *)a.y, (int)a.D, a.N, make_key(a.seed), lsd0,
+                               exp(-lsd0), (const double *)a.q_params, (double *)a.lw_out, (double *)a.lat_out, a.part);
         } else {
-            hipLaunchKernelGGL(gmm_is_kernel<false>, dim3((unsigned)blocks), dim3(kPropThreads), 0, st,
-                               (const float *)a.y, (int)a.D, a.dim, a.N, make_key(a.seed), a.hyper[0], a.hyper[1],
-                               nullptr, (double *)a.lw_out, (double *)a.lat_out, a.part);
+            GmmConst g;
+            double f = 1.0;                      // (K - 1)!
+            for (int k = 2; k < a.dim; ++k) f *= k;
+            g.mu_sd = a.hyper[0];
+            g.lfact = log(f) + log(f * a.dim);
+            g.lmu = log(a.hyper[0]);
+            g.imu = exp(-g.lmu);
+            g.cst = -kHalfLog2PiD - log(a.hyper[1]);
+            g.hisd = 0.5f * (float)(1.0 / a.hyper[1]);
+            switch (a.dim) {
+                case 1: launch_gmm_is<1>(a, blocks, g, st); break;
+                case 2: launch_gmm_is<2>(a, blocks, g, st); break;
+                case 3: launch_gmm_is<3>(a, blocks, g, st); break;
+                case 4: launch_gmm_is<4>(a, blocks, g, st); break;
+                case 5: launch_gmm_is<5>(a, blocks, g, st); break;
+                case 6: launch_gmm_is<6>(a, blocks, g, st); break;
+                case 7: launch_gmm_is<7>(a, blocks, g, st); break;
+                default: launch_gmm_is<8>(a, blocks, g, st); break;
+            }
         }
         timer.stop();
         PPL_LAUNCH_CHECK(name);

@@ -145,3 +145,71 @@ def test_poly_shapes(ppl, orc, D, n_lo, n_hi):
             want = (sel * c).sum(1) / sel.sum() if sel.sum() > 0 else np.zeros(5)
             assert np.all(np.abs(summ[4 + 5 * s:9 + 5 * s] - want) <= tol * 100)
         assert np.all(np.abs(summ[24:] - (w * c).sum(1) / w.sum()) <= tol * 100)
+
+
+# ----------------------------------------------- mixture-proposal kernels --
+def _poly_q(seed=3):
+    """A decoded polynomial proposal with spread means and scales of both sizes."""
+    g = np.random.default_rng(seed)
+    ls = lambda v: v - np.log(np.exp(v).sum())
+    return np.concatenate([ls(g.standard_normal(4)), ls(g.standard_normal(8)), g.standard_normal(160),
+                           g.uniform(-2.0, 1.0, 160)])
+
+
+@pytest.mark.parametrize("D", [1, 7, 8, 63, 64, 511, 512, 513, 600])
+def test_poly_mix_shapes(ppl, orc, D):
+    """Points around the group's stride and the LDS chunk, particle counts on
+    both sides of the rule for eight lanes per particle.  The likelihood is a sum
+    of D terms of one sign and the proposal density one of eight, in another
+    order: the log-weights agree within (D + 32) 2^-52 of the terms' size."""
+    import torch
+    from oracle import proposal
+    x, y = synthetic.poly_data(D=D, seed=90 + D)
+    data = ppl.make_data(torch.from_numpy(x).cuda(), torch.from_numpy(y).cuda())
+    q = _poly_q()
+    dq, seed, ref = torch.from_numpy(q).cuda(), 21, None
+    for n in (16_385, 16_384, 4096, 33, 32, 1):
+        lw = torch.empty(n, dtype=torch.float64, device="cuda")
+        lat = torch.empty((6, n), dtype=torch.float64, device="cuda")
+        summ = torch.empty(29, dtype=torch.float64, device="cuda")
+        ppl.ppl_importance(ppl.PPL_MODEL_POLY, data, n, seed, q=dq, q_kind=ppl.PPL_Q_POLY_MIX, log_weights=lw,
+                           latents=lat, summaries=summ)
+        lw, lat, summ = (t.cpu().numpy() for t in (lw, lat, summ))
+        if ref is None:
+            ref = lw, lat
+            rlw = proposal.propose_poly(seed, q, x, y, np.arange(200))[0]
+            assert np.max(np.abs(lw[:200] - rlw) / np.maximum(1.0, np.abs(rlw))) < 1e-10
+        np.testing.assert_array_equal(lat, ref[1][:, :n])
+        assert np.all(np.abs(lw - ref[0][:n]) <= (D + 32) * 2.0 ** -52 * (np.abs(ref[0][:n]) + 100.0))
+        w = np.exp(lw - lw.max())
+        c = lat[1:]
+        assert np.all(np.abs(summ[24:] - (w * c).sum(1) / w.sum()) <= 1e-9 * np.maximum(1.0, np.abs(summ[24:])))
+        for s in range(4):
+            assert abs(summ[s] - w[lat[0] == s + 2].sum() / w.sum()) <= 1e-10
+
+
+@pytest.mark.parametrize("K", range(1, 9))
+def test_gmm_proposal_components(ppl, orc, K):
+    """Every component count's kernel against the oracle (FP32 likelihood: the
+    1e-5 class), a data count with and without a remainder of the 16-point blocks."""
+    import torch
+    from oracle import proposal
+    g = np.random.default_rng(K)
+    d = 2 * K - 1
+    mix = g.standard_normal(8)
+    q = np.concatenate([mix - np.log(np.exp(mix).sum()), g.standard_normal(8 * d), g.uniform(-1.5, 0.5, 8 * d)])
+    for D in (16, 37):
+        y = synthetic.gmm_learn_data(K=K, D=D, seed=60 + K)
+        data = ppl.make_data(None, torch.from_numpy(y).cuda(), dim=K, dtype=ppl.PPL_F32)
+        n = 700
+        lw = torch.empty(n, dtype=torch.float64, device="cuda")
+        lat = torch.empty((2 * K, n), dtype=torch.float64, device="cuda")
+        ppl.ppl_importance(ppl.PPL_MODEL_GMM, data, n, 5, q=torch.from_numpy(q).cuda(), q_kind=ppl.PPL_Q_GMM_MIX,
+                           log_weights=lw, latents=lat)
+        ref = proposal.propose_gmm(5, q, K, y, np.arange(n))[0]
+        assert np.max(np.abs(lw.cpu().numpy() - ref) / np.maximum(1.0, np.abs(ref))) < 1e-5
+        prior = torch.empty(n, dtype=torch.float64, device="cuda")
+        ppl.ppl_importance(ppl.PPL_MODEL_GMM, data, n, 5, log_weights=prior)
+        ref = proposal.gmm_prior_lw(5, K, y, np.arange(n))
+        ref = ref[0] if isinstance(ref, tuple) else ref
+        assert np.max(np.abs(prior.cpu().numpy() - ref) / np.maximum(1.0, np.abs(ref))) < 1e-5
