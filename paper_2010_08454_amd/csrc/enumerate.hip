@@ -14,24 +14,30 @@
 // prefix) are fanned out over threads, a prefix per thread and 128 prefixes
 // per tile, workgroups striding over the tiles; a thread resumes its prefix
 // for every value of the last Ts sites in nested loops fixed at compile time.
-// Two passes over the paths: the first finds the largest log-weight M and the
-// most probable path (the lowest index among equals), the second sums
-// exp(lw - M) in total and per (t, z_t): the nested sites' sums in
-// registers, the prefix sites' per tile through LDS into one owner thread per
-// (t, k).  Records are merged in workgroup order, so results do not depend on
-// timing.
+// One pass over the paths sums exp(lw - R) in total and per (t, z_t), R a scale
+// near the largest log-weight (enum_emission_kernel), and finds the prefix that
+// holds the heaviest path: the nested sites' sums in registers, the prefix
+// sites' per tile through LDS into one owner thread per (t, k).  Records are
+// merged in a fixed order, so results do not depend on timing.
 //
-// The nested sites run in two forms.  Pass 1 stays in the log domain: one
-// add and one max per path.  Pass 2 runs in the linear domain from one exp
-// per prefix: each node carries the weight, relative to M, of the best path
-// below it, w = exp(lw_node + V_L[z] - M) <= 1, where V_L[j] is the largest
-// log-weight any completion from state j at nested level L can add (a max
-// over the suffix, tabulated per state).  A child's weight is the parent's
-// times F_L[j][k] = exp(c + V_{L+1}[k] - V_L[j]) <= 1, so no product
-// overflows, and a product that underflows belongs to a subtree whose every
-// path is below e^-745 of M.  The references set the scale only: every path's
-// weight is still formed and added (two FMAs at the last site: into its
-// site sum and into the parent's subtotal).
+// The pass runs in the linear domain from one exp per prefix: each node carries
+// the weight, relative to R, of the best path below it, w = exp(lw_node +
+// V_L[z] - R), where V_L[j] is the largest log-weight any completion from state
+// j at nested level L can add (a max over the suffix, tabulated per state).  A
+// child's weight is the parent's times F_L[j][k] = exp(c + V_{L+1}[k] - V_L[j])
+// <= 1, so no product overflows, and a product that underflows belongs to a
+// subtree whose every path is below e^-745 of the best.  The references set the
+// scale only: every path's weight is still formed and added, and every last
+// parent's weight (its heaviest path's) compared.
+//
+// The most probable path and its log joint are those of the log domain: lw
+// summed site by site, the largest, the lowest index among equals.  The linear
+// weights differ from exp of those sums by rounding, so they only select: if
+// one prefix's heaviest weight beats every other prefix's by more than all
+// rounding can account for, that prefix alone is walked in the log domain
+// (enum_pick_kernel); otherwise every path is (enum_max_kernel, which returns
+// at once in the first case).  Near-ties between prefixes, observations that
+// make every path impossible and NaN take the second way.
 #include "device.h"
 #include "host.h"
 #include "kernels.h"
@@ -54,9 +60,10 @@ struct EnumDev {
     uint64_t n_tiles;            // ceil(n_prefix / kEnThreads)
     const double *le;            // [T][K] log emission densities
     double lpi[8], lA[64];
-    double *rec1;                // [grid][2] pass-1 records {best lw, best index (bits)}
-    double *glob;                // [3] {M, best index (bits), non-finite}
-    double *rec2;                // [grid][1 + T K] pass-2 records {total, per-site sums}
+    double *rec1;                // [grid][2] {heaviest weight, negated beside a near-tie; its prefix (bits)}, then
+                                 // from enum_max_kernel {best lw, best index (bits)}
+    double *glob;                // [6] {scale R, near-tie margin, non-finite, 1 if the path is found, M, best index (bits)}
+    double *rec2;                // [grid][1 + T K] records {total, per-site sums}
 };
 
 struct EnLds {
@@ -132,7 +139,7 @@ __device__ __forceinline__ double en_prefix(const EnLds &s, int tail, uint64_t p
     return lw;
 }
 
-// ---- pass 1 (log domain).  Levels above TS - UL are runtime loops; the last
+// ---- log domain.  Levels above TS - UL are runtime loops; the last
 // UL levels are unrolled, so their table rows are compile-time indices.
 template <int K, int L, int TS, int UL>
 struct WalkMax {
@@ -200,17 +207,52 @@ __device__ uint64_t en_locate(const EnLds &s, int tail, uint64_t p, uint64_t nod
     return (p * ipow(K, NL) + node) * n + m;
 }
 
-// ---- pass 2 (linear domain): returns the sum of the path weights below the
-// node and adds each nested site's share to marg.
+// ---- linear domain.  Factors of the last levels (those whose parent state is
+// a compile-time index) in scalar registers, as far as 36 values go: a
+// v_fma_f64 with a scalar operand reads two vector register pairs instead of
+// three, and 72 fewer vector registers leave room for a third wave per SIMD.
+// Bound: FP64 issue, 2.45 vector instructions per path (4 states: the FMA, a
+// quarter each of the parent's weight, its subtotal twice and its maximum, and
+// the levels above), 0.72 of the rate at 4 states x 20 steps: 95 ms a call for
+// 2^40 paths; 146 ms with a maximum pass of its own, factors in vector registers
+// and records added one by one.
+template <int K, int TS, int UL>
+struct ScalarF {
+    static constexpr int kRoom = (36 - K) / (K * K);
+    static constexpr int NS = kRoom < UL - 1 ? (kRoom > 0 ? kRoom : 0) : (UL > 1 ? UL - 1 : 0);   // levels held
+    double f[NS > 0 ? NS * K * K : 1], g[K];
+    __device__ __forceinline__ void load(const EnLds &s) {
+        if constexpr (NS > 0) {
+#pragma unroll
+            for (int i = 0; i < NS * K * K; ++i) f[i] = uniform(s.F[(TS - NS) * K * K + i]);
+#pragma unroll
+            for (int k = 0; k < K; ++k) g[k] = uniform(s.G[(TS - 1) * K + k]);
+        }
+    }
+    __device__ __forceinline__ static double uniform(double v) {
+        const uint64_t b = __builtin_bit_cast(uint64_t, v);
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b);
+        const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32));
+        return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+    }
+};
+
+// Returns the sum of the path weights below the node, adds each nested site's
+// share to marg and raises wm to the heaviest path's weight.
 template <int K, int L, int TS, int UL>
 struct WalkSum {
-    __device__ static double run(const EnLds &s, int prev, double w, double (&marg)[TS][K]) {
-        const double *F = s.F + (L * K + prev) * K;
+    using SF = ScalarF<K, TS, UL>;
+    __device__ static double run(const EnLds &s, const SF &sf, int prev, double w, double (&marg)[TS][K], double &wm) {
+        constexpr bool scalar = L >= TS - SF::NS;
+        auto F = [&](int k) {
+            if constexpr (scalar) return sf.f[((L - (TS - SF::NS)) * K + prev) * K + k];
+            else return s.F[(L * K + prev) * K + k];
+        };
         double tot = 0.0;
         if constexpr (L < TS - UL) {
 #pragma unroll 1
             for (int k = 0; k < K; ++k) {
-                const double sub = WalkSum<K, L + 1, TS, UL>::run(s, k, w * F[k], marg);
+                const double sub = WalkSum<K, L + 1, TS, UL>::run(s, sf, k, w * F(k), marg, wm);
 #pragma unroll
                 for (int kk = 0; kk < K; ++kk) marg[L][kk] += (k == kk) ? sub : 0.0;
                 tot += sub;
@@ -218,14 +260,17 @@ struct WalkSum {
         } else if constexpr (L == TS - 1) {
             // each path's weight w F[k] goes into its site sum; the node's
             // subtotal, their sum, is w times the row sum G (one product for
-            // the K paths)
+            // the K paths); the heaviest of them is w itself (the largest F of
+            // a row is 1)
 #pragma unroll
-            for (int k = 0; k < K; ++k) marg[L][k] = fma(w, F[k], marg[L][k]);
-            tot = w * s.G[L * K + prev];
+            for (int k = 0; k < K; ++k) marg[L][k] = fma(w, F(k), marg[L][k]);
+            wm = fmax(wm, w);
+            if constexpr (scalar) tot = w * sf.g[prev];
+            else tot = w * s.G[L * K + prev];
         } else {
 #pragma unroll
             for (int k = 0; k < K; ++k) {
-                const double sub = WalkSum<K, L + 1, TS, UL>::run(s, k, w * F[k], marg);
+                const double sub = WalkSum<K, L + 1, TS, UL>::run(s, sf, k, w * F(k), marg, wm);
                 marg[L][k] += sub;
                 tot += sub;
             }
@@ -234,12 +279,14 @@ struct WalkSum {
     }
 };
 
-// Pass 1: the largest log-weight and its path.
+// Every path in the log domain: the largest log-weight and its path.  Only if
+// enum_pick_kernel could not tell the prefix from the weights.
 template <int K, int TS, int UL>
 __global__ __launch_bounds__(kEnThreads) void enum_max_kernel(EnumDev a) {
     __shared__ EnLds s;
     __shared__ double s_best[kEnThreads];
     __shared__ uint64_t s_idx[kEnThreads];
+    if (a.glob[3] != 0.0) return;
     en_stage<K, TS>(s, a, false);
     double best = -INFINITY;
     uint64_t bidx = 0, bp = 0, bnode = 0;
@@ -276,50 +323,112 @@ __global__ __launch_bounds__(kEnThreads) void enum_max_kernel(EnumDev a) {
     }
 }
 
-// Merges the pass-1 records (the largest log-weight, the lowest index among
-// equals) and flags a NaN emission term (a NaN observation makes every path's
-// log-weight NaN).  One workgroup.
-__global__ __launch_bounds__(256) void enum_merge_kernel(const double *__restrict__ rec1, int nrec,
-                                                         const double *__restrict__ le, int n_le,
-                                                         double *__restrict__ glob) {
+// The prefix of the heaviest path, if the weights tell it apart (no other
+// prefix within the margin), walked in the log domain: the largest of its
+// log-weights and the lowest index that reaches it.  One workgroup; a thread
+// takes whole last parents, whose log-weights are summed in the walk's order.
+template <int K, int TS>
+__global__ __launch_bounds__(256) void enum_pick_kernel(EnumDev a, int nrec) {
+    __shared__ EnLds s;
     __shared__ double s_best[256];
     __shared__ uint64_t s_idx[256];
-    __shared__ int s_bad;
-    if (threadIdx.x == 0) s_bad = 0;
-    __syncthreads();
-    double bl = -INFINITY;
-    uint64_t bi = 0;
+    __shared__ int s_near;
+    // the heaviest record, and how many are within the margin of it
+    double wb = 0.0;
+    uint64_t p = 0;
     for (int r = threadIdx.x; r < nrec; r += 256) {
-        const double b = rec1[2 * (size_t)r];
-        const uint64_t i = (uint64_t)__double_as_longlong(rec1[2 * (size_t)r + 1]);
-        if (b > bl || (b == bl && i < bi)) { bl = b; bi = i; }
+        const double w = fabs(a.rec1[2 * (size_t)r]);
+        if (w > wb) {
+            wb = w;
+            p = (uint64_t)__double_as_longlong(a.rec1[2 * (size_t)r + 1]);
+        }
     }
-    int bad = 0;
-    for (int i = threadIdx.x; i < n_le; i += 256) bad |= le[i] != le[i];
-    if (bad) atomicOr(&s_bad, 1);
-    s_best[threadIdx.x] = bl;
-    s_idx[threadIdx.x] = bi;
+    if (threadIdx.x == 0) s_near = 0;
+    s_best[threadIdx.x] = wb;
+    s_idx[threadIdx.x] = p;
     __syncthreads();
+    for (int o = 128; o > 0; o >>= 1) {
+        if ((int)threadIdx.x < o && s_best[threadIdx.x + o] > s_best[threadIdx.x]) {
+            s_best[threadIdx.x] = s_best[threadIdx.x + o];
+            s_idx[threadIdx.x] = s_idx[threadIdx.x + o];
+        }
+        __syncthreads();
+    }
+    wb = s_best[0];
+    p = s_idx[0];
+    const double margin = a.glob[1], least = wb * (1.0 - margin);
+    int near = 0;
+    for (int r = threadIdx.x; r < nrec; r += 256) {
+        const double w = a.rec1[2 * (size_t)r];
+        if (fabs(w) >= least) near += w < 0.0 ? 2 : 1;
+    }
+    if (near) atomicAdd(&s_near, near);
+    __syncthreads();
+    const bool found = wb > 0.0 && wb < INFINITY && margin < 0.5 && s_near == 1 && a.glob[2] == 0.0;
+    if (threadIdx.x == 0) a.glob[3] = found ? 1.0 : 0.0;
+    if (!found) return;
+    en_stage<K, TS>(s, a, false);
+    double best = -INFINITY;
+    uint64_t bidx = 0;
+    if constexpr (TS == 0) {
+        int last;
+        best = en_prefix<K>(s, a.tail, p, last);
+        bidx = p;
+    } else {
+        constexpr int n = (int)ipow(K, TS - 1);      // last parents of the prefix
+        int last;
+        const double lw0 = en_prefix<K>(s, a.tail, p, last);
+        for (int m = threadIdx.x; m < n; m += 256) {
+            double x = lw0;
+            int pv = last, r = m;
+#pragma unroll
+            for (int L = 0, dv = n / K; L < TS - 1; ++L, dv /= K) {
+                const int k = r / dv;
+                r -= k * dv;
+                x = x + s.cn[(L * K + pv) * K + k];
+                pv = k;
+            }
+            const double v = x + s.cm[pv];
+            if (v > best) {
+                int k = 0;
+                for (; k < K - 1; ++k)
+                    if (x + s.cn[((TS - 1) * K + pv) * K + k] == v) break;
+                best = v;
+                bidx = (p * n + m) * K + k;
+            }
+        }
+    }
+    s_best[threadIdx.x] = best;
+    s_idx[threadIdx.x] = bidx;
+    __syncthreads();
+    for (int o = 128; o > 0; o >>= 1) {
+        if ((int)threadIdx.x < o) {
+            const double v = s_best[threadIdx.x + o];
+            const uint64_t i = s_idx[threadIdx.x + o];
+            if (v > s_best[threadIdx.x] || (v == s_best[threadIdx.x] && i < s_idx[threadIdx.x])) {
+                s_best[threadIdx.x] = v;
+                s_idx[threadIdx.x] = i;
+            }
+        }
+        __syncthreads();
+    }
     if (threadIdx.x == 0) {
-        for (int i = 1; i < 256; ++i)
-            if (s_best[i] > bl || (s_best[i] == bl && s_idx[i] < bi)) { bl = s_best[i]; bi = s_idx[i]; }
-        glob[0] = bl;
-        glob[1] = __longlong_as_double((long long)bi);
-        glob[2] = s_bad ? 1.0 : 0.0;
+        a.glob[4] = s_best[0];
+        a.glob[5] = __longlong_as_double((long long)s_idx[0]);
     }
 }
 
-// Pass 2: sums of exp(lw - M) in total and per (t, z_t).
+// Sums of exp(lw - R) in total and per (t, z_t), and the heaviest path's prefix.
 template <int K, int TS, int UL>
-__global__ __launch_bounds__(kEnThreads) void enum_sum_kernel(EnumDev a) {
+__global__ __launch_bounds__(kEnThreads, 2) void enum_sum_kernel(EnumDev a) {
     constexpr int TSA = TS > 0 ? TS : 1;
     constexpr int kWaves = kEnThreads / 64;
     __shared__ EnLds s;
     __shared__ double s_sub[kEnThreads];
     __shared__ double s_wsum[kWaves];
     en_stage<K, TS>(s, a, true);
-    const double M = a.glob[0];
-    const bool skip = !(M > -INFINITY) || a.glob[2] != 0.0;
+    const double R = a.glob[0];
+    const bool skip = !(R > -INFINITY) || a.glob[2] != 0.0;
     const int tail = a.tail, T = a.T;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     double *rec = a.rec2 + (size_t)blockIdx.x * (1 + T * K);
@@ -333,7 +442,11 @@ __global__ __launch_bounds__(kEnThreads) void enum_sum_kernel(EnumDev a) {
     for (int l = 0; l < TSA; ++l)
 #pragma unroll
         for (int k = 0; k < K; ++k) marg[l][k] = 0.0;
+    ScalarF<K, TSA, UL> sf;
+    if constexpr (TS > 0) sf.load(s);
     double tot = 0.0;
+    double best = 0.0, second = 0.0;             // heaviest weights of two prefixes of this thread
+    uint64_t best_p = 0;
     for (uint64_t tile = blockIdx.x; !skip && tile < a.n_tiles; tile += gridDim.x) {
         const uint64_t base = tile * kEnThreads;
         const uint64_t p = base + threadIdx.x;
@@ -341,11 +454,19 @@ __global__ __launch_bounds__(kEnThreads) void enum_sum_kernel(EnumDev a) {
         if (p < a.n_prefix) {
             int last;
             const double lw = en_prefix<K>(s, tail, p, last);
+            double wm = 0.0;
             if constexpr (TS == 0) {
-                sub = exp(lw - M);
+                sub = wm = exp(lw - R);
             } else {
-                const double w = exp(lw + s.V[last] - M);      // the best path below the prefix, <= 1
-                sub = WalkSum<K, 0, TS, UL>::run(s, last, w, marg);
+                const double w = exp(lw + s.V[last] - R);      // the best path below the prefix, near 1 at most
+                sub = WalkSum<K, 0, TS, UL>::run(s, sf, last, w, marg, wm);
+            }
+            if (wm > best) {
+                second = best;
+                best = wm;
+                best_p = p;
+            } else {
+                second = fmax(second, wm);
             }
         }
         tot += sub;
@@ -397,63 +518,117 @@ __global__ __launch_bounds__(kEnThreads) void enum_sum_kernel(EnumDev a) {
         const int e = threadIdx.x + j * kEnThreads;
         if (e < tail * K) rec[1 + e] = own[j];
     }
-    // the total and the nested sites, one value at a time through LDS, thread order
-    s_sub[threadIdx.x] = tot;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double acc = 0.0;
-        for (int i = 0; i < kEnThreads; ++i) acc += s_sub[i];
-        rec[0] = acc;
+    // the total and the nested sites: wave sums, then the waves in order
+    __shared__ double s_tot[kWaves][1 + TSA * K];
+    {
+        const double v = wave_sum_dpp(tot);
+        if (lane == 0) s_tot[wave][0] = v;
     }
 #pragma unroll
-    for (int l = 0; l < TS; ++l) {
+    for (int l = 0; l < TS; ++l)
 #pragma unroll
         for (int k = 0; k < K; ++k) {
-            __syncthreads();
-            s_sub[threadIdx.x] = marg[l][k];
-            __syncthreads();
-            if (threadIdx.x == 0) {
-                double acc = 0.0;
-                for (int i = 0; i < kEnThreads; ++i) acc += s_sub[i];
-                rec[1 + (tail + l) * K + k] = acc;
+            const double v = wave_sum_dpp(marg[l][k]);
+            if (lane == 0) s_tot[wave][1 + l * K + k] = v;
+        }
+    // the heaviest prefix of the workgroup; negated where another is within the margin
+    __shared__ double s_best[kEnThreads], s_second[kEnThreads];
+    __shared__ uint64_t s_p[kEnThreads];
+    s_best[threadIdx.x] = best;
+    s_second[threadIdx.x] = second;
+    s_p[threadIdx.x] = best_p;
+    __syncthreads();
+    for (int o = kEnThreads / 2; o > 0; o >>= 1) {
+        if ((int)threadIdx.x < o) {
+            const double b = s_best[threadIdx.x + o];
+            s_second[threadIdx.x] = fmax(fmax(s_second[threadIdx.x], s_second[threadIdx.x + o]), fmin(s_best[threadIdx.x], b));
+            if (b > s_best[threadIdx.x]) {
+                s_best[threadIdx.x] = b;
+                s_p[threadIdx.x] = s_p[threadIdx.x + o];
             }
         }
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) {
+        const bool near = s_second[0] >= s_best[0] * (1.0 - a.glob[1]);
+        a.rec1[2 * (size_t)blockIdx.x] = near ? -s_best[0] : s_best[0];
+        a.rec1[2 * (size_t)blockIdx.x + 1] = __longlong_as_double((long long)s_p[0]);
+    }
+    for (int e = threadIdx.x; e < 1 + TS * K; e += kEnThreads) {
+        double v = s_tot[0][e];
+#pragma unroll
+        for (int w = 1; w < kWaves; ++w) v += s_tot[w][e];
+        rec[e == 0 ? 0 : tail * K + e] = v;
     }
 }
 
-// Merges the pass-2 records in record order: scal[4] = {log Z, paths, log
-// joint of the most probable path, status}, marg[T][K] = P(z_t = k | y),
-// map[T] the most probable path.
+// Merges the records: scal[4] = {log Z, paths, log joint of the most probable
+// path, status}, marg[T][K] = P(z_t = k | y), map[T] the most probable path.
+// Workgroup f merges value f of the records (and all of them the total, 0),
+// thread t adding records t, t + 256, ... and the threads in a fixed order: one
+// workgroup adding them all in turn took 0.87 ms.
 __global__ __launch_bounds__(256) void enum_finalize_kernel(const double *__restrict__ rec2, int nrec, int K, int T,
-                                                            double paths, const double *__restrict__ glob,
+                                                            double paths, const double *__restrict__ rec1,
+                                                            const double *__restrict__ glob,
                                                             double *__restrict__ scal, double *__restrict__ marg,
                                                             int32_t *__restrict__ map) {
-    __shared__ double s_tot;
-    const int rl = 1 + T * K;
-    const double M = glob[0];
-    const int status = glob[2] != 0.0 ? PPL_E_NONFINITE : M > -INFINITY ? PPL_OK : PPL_E_ZERO_WEIGHT;
-    if (threadIdx.x == 0) {
-        double acc = 0.0;
-        for (int r = 0; r < nrec; ++r) acc += rec2[(size_t)r * rl];
-        s_tot = acc;
+    __shared__ double s_sum[2][4], s_best[256];
+    __shared__ uint64_t s_idx[256];
+    const int rl = 1 + T * K, f = blockIdx.x;
+    double tot = 0.0, acc = 0.0, M = -INFINITY;
+    uint64_t bi = 0;
+    const bool found = glob[3] != 0.0;
+    for (int r = threadIdx.x; r < nrec; r += 256) {
+        const double *rec = rec2 + (size_t)r * rl;
+        tot += rec[0];
+        acc += rec[f];
+        if (!found) {
+            const double b = rec1[2 * (size_t)r];
+            const uint64_t i = (uint64_t)__double_as_longlong(rec1[2 * (size_t)r + 1]);
+            if (b > M || (b == M && i < bi)) { M = b; bi = i; }
+        }
     }
+    tot = wave_sum_dpp(tot);
+    acc = wave_sum_dpp(acc);
+    if ((threadIdx.x & 63) == 0) {
+        s_sum[0][threadIdx.x >> 6] = tot;
+        s_sum[1][threadIdx.x >> 6] = acc;
+    }
+    s_best[threadIdx.x] = M;
+    s_idx[threadIdx.x] = bi;
     __syncthreads();
-    const double tot = s_tot;
-    if (marg)
-        for (int f = threadIdx.x; f < T * K; f += blockDim.x) {
-            double acc = 0.0;
-            for (int r = 0; r < nrec; ++r) acc += rec2[(size_t)r * rl + 1 + f];
-            marg[f] = status == PPL_OK ? acc / tot : 0.0;
+    if (found) {
+        M = glob[4];
+        bi = (uint64_t)__double_as_longlong(glob[5]);
+    } else {
+        for (int o = 128; o > 0; o >>= 1) {
+            if ((int)threadIdx.x < o) {
+                const double b = s_best[threadIdx.x + o];
+                const uint64_t i = s_idx[threadIdx.x + o];
+                if (b > s_best[threadIdx.x] || (b == s_best[threadIdx.x] && i < s_idx[threadIdx.x])) {
+                    s_best[threadIdx.x] = b;
+                    s_idx[threadIdx.x] = i;
+                }
+            }
+            __syncthreads();
         }
-    if (threadIdx.x == 0) {
-        scal[0] = status == PPL_OK ? M + log(tot) : status == PPL_E_NONFINITE ? NAN : -INFINITY;
-        scal[1] = paths;
-        scal[2] = status == PPL_OK ? M : scal[0];
-        scal[3] = (double)status;
-        if (map) {
-            uint64_t q = (uint64_t)__double_as_longlong(glob[1]);
-            for (int t = T - 1; t >= 0; --t) { map[t] = (int32_t)(q % (uint64_t)K); q /= (uint64_t)K; }
-        }
+        M = s_best[0];
+        bi = s_idx[0];
+    }
+    if (threadIdx.x != 0) return;
+    tot = (s_sum[0][0] + s_sum[0][1]) + (s_sum[0][2] + s_sum[0][3]);
+    acc = (s_sum[1][0] + s_sum[1][1]) + (s_sum[1][2] + s_sum[1][3]);
+    const int status = glob[2] != 0.0 ? PPL_E_NONFINITE : M > -INFINITY ? PPL_OK : PPL_E_ZERO_WEIGHT;
+    if (f > 0) {
+        if (marg) marg[f - 1] = status == PPL_OK ? acc / tot : 0.0;
+        return;
+    }
+    scal[0] = status == PPL_OK ? glob[0] + log(tot) : status == PPL_E_NONFINITE ? NAN : -INFINITY;
+    scal[1] = paths;
+    scal[2] = status == PPL_OK ? M : scal[0];
+    scal[3] = (double)status;
+    if (map) {
+        for (int t = T - 1; t >= 0; --t) { map[t] = (int32_t)(bi % (uint64_t)K); bi /= (uint64_t)K; }
     }
 }
 
@@ -462,14 +637,61 @@ struct EnEmission {
     double sigma;
 };
 
-// log emission densities le[t][k] = log Normal(y_t; mu_k, sigma).
-__global__ void enum_emission_kernel(const double *__restrict__ y, int T, int K, EnEmission e,
-                                     double *__restrict__ le) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= T * K) return;
-    const int t = i / K, k = i % K;
-    const double r = (y[t] - e.mu[k]) / e.sigma;
-    le[i] = -0.5 * log(2.0 * M_PI) - log(e.sigma) - 0.5 * r * r;
+// log emission densities le[t][k] = log Normal(y_t; mu_k, sigma), and what the
+// walk needs of the whole chain: the scale R, the largest log-weight up to
+// rounding (a max per site and state), a flag for a NaN emission (it makes every
+// path's log-weight NaN) and the near-tie margin, a bound of the rounding error
+// that the linear weights and the log-domain sums can differ by: 2^-44 (T adds
+// and as many factors, each within 2^-52 of partial sums below S) times S, the
+// sum over the sites of their largest finite |c_t|, and 1e-9.  One workgroup.
+__global__ __launch_bounds__(256) void enum_emission_kernel(const double *__restrict__ y, EnumDev a, int K,
+                                                            EnEmission e, double *__restrict__ le,
+                                                            double *__restrict__ glob) {
+    __shared__ double s_le[kEnMaxC], s_v[2][8], s_size[256];
+    __shared__ int s_bad;
+    const int n = a.T * K;
+    if (threadIdx.x == 0) s_bad = 0;
+    __syncthreads();
+    int bad = 0;
+    for (int i = threadIdx.x; i < n; i += 256) {
+        const int t = i / K, k = i % K;
+        const double r = (y[t] - e.mu[k]) / e.sigma;
+        const double v = -0.5 * log(2.0 * M_PI) - log(e.sigma) - 0.5 * r * r;
+        le[i] = v;
+        s_le[i] = v;
+        bad |= v != v;
+    }
+    if (bad) atomicOr(&s_bad, 1);
+    __syncthreads();
+    double size = 0.0;
+    for (int t = threadIdx.x; t < a.T; t += 256) {
+        double m = 0.0;
+        for (int j = 0; j < (t == 0 ? 1 : K); ++j)
+            for (int k = 0; k < K; ++k) {
+                const double c = fabs((t == 0 ? a.lpi[k] : a.lA[j * K + k]) + s_le[t * K + k]);
+                if (c < INFINITY) m = fmax(m, c);
+            }
+        size += m;
+    }
+    s_size[threadIdx.x] = size;
+    if ((int)threadIdx.x < K) s_v[0][threadIdx.x] = a.lpi[threadIdx.x] + s_le[threadIdx.x];
+    for (int t = 1; t < a.T; ++t) {
+        __syncthreads();
+        if ((int)threadIdx.x < K) {
+            double v = -INFINITY;
+            for (int j = 0; j < K; ++j) v = fmax(v, s_v[(t - 1) & 1][j] + a.lA[j * K + threadIdx.x]);
+            s_v[t & 1][threadIdx.x] = v + s_le[t * K + threadIdx.x];
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double R = -INFINITY, S = 0.0;
+        for (int k = 0; k < K; ++k) R = fmax(R, s_v[(a.T - 1) & 1][k]);
+        for (int i = 0; i < a.T; ++i) S += s_size[i];
+        glob[0] = R;
+        glob[1] = 1e-9 + 0x1p-44 * S;
+        glob[2] = s_bad ? 1.0 : 0.0;
+    }
 }
 
 // ---------------------------------------------------------------- host --
@@ -494,7 +716,7 @@ static int en_plan(int K, int T, EnPlan &p) {
     return PPL_OK;
 }
 
-// Workspace: [256 scalars][le T K][glob 3][rec1 grid 2][rec2 grid (1 + T K)], each 256-byte aligned.
+// Workspace: [256 scalars][le T K][glob 6][rec1 grid 2][rec2 grid (1 + T K)], each 256-byte aligned.
 size_t enum_ws_bytes(int K, int T) {
     EnPlan p;
     if (en_plan(K, T, p)) return 0;
@@ -502,31 +724,50 @@ size_t enum_ws_bytes(int K, int T) {
            align_up((size_t)p.grid * (1 + T * K) * 8, 256);
 }
 
+// Workgroups of the sum kernel that the device holds at once, at most p.grid:
+// every workgroup takes an equal share of the tiles, so one more round of a
+// few workgroups would leave most SIMDs idle (2048 workgroups where 1536 fit
+// took 113 ms instead of 95 for 4 states x 20 steps).
 template <int K, int TS>
-static int en_launch(const EnumDev &d, const EnPlan &p, hipStream_t st) {
+static int en_sum_grid(const EnPlan &p) {
+    static const int resident = [] {
+        int dev = 0, ncu = 0, per_cu = 0;
+        if (hipGetDevice(&dev) != hipSuccess ||
+            hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, enum_sum_kernel<K, TS, en_ul(K, TS)>, kEnThreads, 0) !=
+                hipSuccess)
+            return 0;
+        return ncu * per_cu;
+    }();
+    return resident > 0 ? std::min(p.grid, resident) : p.grid;
+}
+
+template <int K, int TS>
+static int en_launch(const EnumDev &d, const EnPlan &p, int &nrec, hipStream_t st) {
     constexpr int UL = en_ul(K, TS);
+    nrec = en_sum_grid<K, TS>(p);
     static_assert(TS <= kEnMaxTS && TS * K * K <= kEnMaxF, "nested tables exceed their LDS slots");
     {
-        KernelTimer timer("enum_max_kernel", st);
-        hipLaunchKernelGGL((enum_max_kernel<K, TS, UL>), dim3((unsigned)p.grid), dim3(kEnThreads), 0, st, d);
-        timer.stop();
-    }
-    PPL_LAUNCH_CHECK("enum_max_kernel");
-    hipLaunchKernelGGL(enum_merge_kernel, dim3(1), dim3(256), 0, st, d.rec1, p.grid, d.le, d.T * K, d.glob);
-    PPL_LAUNCH_CHECK("enum_merge_kernel");
-    {
         KernelTimer timer("enum_sum_kernel", st);
-        hipLaunchKernelGGL((enum_sum_kernel<K, TS, UL>), dim3((unsigned)p.grid), dim3(kEnThreads), 0, st, d);
+        hipLaunchKernelGGL((enum_sum_kernel<K, TS, UL>), dim3((unsigned)nrec), dim3(kEnThreads), 0, st, d);
         timer.stop();
     }
     PPL_LAUNCH_CHECK("enum_sum_kernel");
+    hipLaunchKernelGGL((enum_pick_kernel<K, TS>), dim3(1), dim3(256), 0, st, d, nrec);
+    PPL_LAUNCH_CHECK("enum_pick_kernel");
+    {
+        KernelTimer timer("enum_max_kernel", st);
+        hipLaunchKernelGGL((enum_max_kernel<K, TS, UL>), dim3((unsigned)nrec), dim3(kEnThreads), 0, st, d);
+        timer.stop();
+    }
+    PPL_LAUNCH_CHECK("enum_max_kernel");
     return PPL_OK;
 }
 
 template <int K, int TS = en_ts_max(K)>
-static int en_dispatch(const EnumDev &d, const EnPlan &p, hipStream_t st) {
-    if (p.Ts == TS) return en_launch<K, TS>(d, p, st);
-    if constexpr (TS > 0) return en_dispatch<K, TS - 1>(d, p, st);
+static int en_dispatch(const EnumDev &d, const EnPlan &p, int &nrec, hipStream_t st) {
+    if (p.Ts == TS) return en_launch<K, TS>(d, p, nrec, st);
+    if constexpr (TS > 0) return en_dispatch<K, TS - 1>(d, p, nrec, st);
     return fail(PPL_E_UNSUPPORTED, "no enumeration kernel for %d states with %d nested sites", K, p.Ts);
 }
 
@@ -545,8 +786,6 @@ int run_enumerate_hmm(const EnumArgs &a, hipStream_t st) {
     EnEmission em{};
     for (int k = 0; k < K; ++k) em.mu[k] = a.mu[k];
     em.sigma = a.sigma;
-    hipLaunchKernelGGL(enum_emission_kernel, dim3((T * K + 255) / 256), dim3(256), 0, st, a.y, T, K, em, le);
-    PPL_LAUNCH_CHECK("enum_emission_kernel");
     EnumDev d{};
     d.T = T;
     d.tail = p.tail;
@@ -558,20 +797,22 @@ int run_enumerate_hmm(const EnumArgs &a, hipStream_t st) {
     d.rec2 = rec2;
     for (int k = 0; k < K; ++k) d.lpi[k] = log(a.pi0[k]);
     for (int k = 0; k < K * K; ++k) d.lA[k] = log(a.A[k]);
-    int rc = PPL_E_ARG;
+    hipLaunchKernelGGL(enum_emission_kernel, dim3(1), dim3(256), 0, st, a.y, d, K, em, le, glob);
+    PPL_LAUNCH_CHECK("enum_emission_kernel");
+    int rc = PPL_E_ARG, nrec = 0;
     switch (K) {
-        case 1: rc = en_launch<1, 0>(d, p, st); break;
-        case 2: rc = en_dispatch<2>(d, p, st); break;
-        case 3: rc = en_dispatch<3>(d, p, st); break;
-        case 4: rc = en_dispatch<4>(d, p, st); break;
-        case 5: rc = en_dispatch<5>(d, p, st); break;
-        case 6: rc = en_dispatch<6>(d, p, st); break;
-        case 7: rc = en_dispatch<7>(d, p, st); break;
-        case 8: rc = en_dispatch<8>(d, p, st); break;
+        case 1: rc = en_launch<1, 0>(d, p, nrec, st); break;
+        case 2: rc = en_dispatch<2>(d, p, nrec, st); break;
+        case 3: rc = en_dispatch<3>(d, p, nrec, st); break;
+        case 4: rc = en_dispatch<4>(d, p, nrec, st); break;
+        case 5: rc = en_dispatch<5>(d, p, nrec, st); break;
+        case 6: rc = en_dispatch<6>(d, p, nrec, st); break;
+        case 7: rc = en_dispatch<7>(d, p, nrec, st); break;
+        case 8: rc = en_dispatch<8>(d, p, nrec, st); break;
     }
     if (rc) return rc;
-    hipLaunchKernelGGL(enum_finalize_kernel, dim3(1), dim3(256), 0, st, rec2, p.grid, K, T,
-                       (double)ipow((uint64_t)K, T), glob, a.scalars, a.marginals, a.map);
+    hipLaunchKernelGGL(enum_finalize_kernel, dim3((unsigned)(1 + T * K)), dim3(256), 0, st, rec2, nrec, K, T,
+                       (double)ipow((uint64_t)K, T), rec1, glob, a.scalars, a.marginals, a.map);
     PPL_LAUNCH_CHECK("enum_finalize_kernel");
     return PPL_OK;
 }

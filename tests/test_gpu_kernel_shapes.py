@@ -213,3 +213,47 @@ def test_gmm_proposal_components(ppl, orc, K):
         ref = proposal.gmm_prior_lw(5, K, y, np.arange(n))
         ref = ref[0] if isinstance(ref, tuple) else ref
         assert np.max(np.abs(prior.cpu().numpy() - ref) / np.maximum(1.0, np.abs(ref))) < 1e-5
+
+
+# ------------------------------------------------------------ enumeration --
+@pytest.mark.parametrize("K,T", [(2, 1), (2, 13), (3, 8), (4, 7), (5, 6), (6, 6), (7, 5), (8, 5)])
+@pytest.mark.parametrize("gap", [0.0, 1e-14, 1e-10, 1e-3])
+@pytest.mark.parametrize("far", [0.0, 1e4])
+def test_enumerate_near_ties(ppl, orc, K, T, gap, far):
+    """Two states whose means differ by `gap` make every path tie, or nearly,
+    with the paths that swap them, across the prefixes too: the most probable
+    path and its log joint are the oracle's whichever way the search goes
+    (their tolerance: T additions of terms of size |lw|).  `far` puts one
+    observation far out, so that the log-weights are large."""
+    import torch
+    pi0, A, mu, sigma, y, _ = synthetic.hmm_instance(K, T, seed=77)
+    mu = mu.copy()
+    mu[1] = mu[0] + gap
+    A = A.copy()
+    A[1] = A[0]
+    A[:, 1] = A[:, 0]
+    A /= A.sum(1, keepdims=True)
+    pi0 = pi0.copy()
+    pi0[1] = pi0[0]
+    pi0 /= pi0.sum()
+    y = y.copy()
+    y[T // 2] += far
+    o = orc.enumerate_hmm(y, orc.hmm_hyper(pi0, A, mu, sigma))
+    data = ppl.hmm_data(torch.from_numpy(y).cuda(), pi0, A, mu, sigma)
+    scal = torch.empty(4, dtype=torch.float64, device="cuda")
+    marg = torch.empty((T, K), dtype=torch.float64, device="cuda")
+    mp = torch.empty(T, dtype=torch.int32, device="cuda")
+    ppl.ppl_enumerate(ppl.PPL_MODEL_HMM, data, scalars=scal, marginals=marg, map_path=mp)
+    scal, marg, mp = scal.cpu().numpy(), marg.cpu().numpy(), mp.cpu().numpy()
+    tol = (T + 2) * 2.0 ** -51 * max(1.0, abs(o["map_lw"]))
+    assert scal[3] == 0 and abs(scal[2] - o["map_lw"]) <= tol and abs(scal[0] - o["log_z"]) <= tol + 2e-9
+
+    def lw(z):
+        r = (y - mu[z]) / sigma
+        return (np.log(pi0[z[0]]) + np.log(A[z[:-1], z[1:]]).sum()
+                + (-0.5 * np.log(2 * np.pi) - np.log(sigma) - 0.5 * r * r).sum())
+    assert abs(lw(mp) - o["map_lw"]) <= 2 * tol
+    if gap == 0.0:
+        assert 1 not in mp                        # the lowest index among equals
+    if far == 0.0:
+        assert np.max(np.abs(marg - o["marginals"])) <= 2e-9
