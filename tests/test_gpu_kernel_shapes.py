@@ -257,3 +257,49 @@ def test_enumerate_near_ties(ppl, orc, K, T, gap, far):
         assert 1 not in mp                        # the lowest index among equals
     if far == 0.0:
         assert np.max(np.abs(marg - o["marginals"])) <= 2e-9
+
+
+# ------------------------------------------------------ Metropolis-Hastings --
+@pytest.mark.parametrize("D", [0, 1, 3, 5, 16, 20, 31, 32, 63, 64, 100, 2048, 2049])
+@pytest.mark.parametrize("n_lo,n_hi", [(2, 5), (1, 4)])
+def test_mcmc_shapes(ppl, D, n_lo, n_hi):
+    """Chains on both sides of the rule for four lanes per chain, point counts
+    around its stride and the scalar batches.  A chain depends only on its index:
+    the same trace and state whichever kernel runs it (a likelihood sum in
+    another order, D terms of one sign, moves log alpha by at most D 2^-52 |ll|;
+    no decision here lies that close)."""
+    import torch
+    x, y = synthetic.poly_data(D=max(D, 1), seed=300 + D)
+    dx, dy = torch.from_numpy(x[:D].copy()).cuda(), torch.from_numpy(y[:D].copy()).cuda()
+    hyper = [10.0, n_lo, n_hi]
+    data = ppl.make_data(dx, dy, n_data=D, hyper=hyper, dtype=ppl.PPL_F64)
+    if D == 0:
+        data.x = data.y = None
+    T, burn, seed, ref = 20, 5, 13, None
+    for C in (32_769, 32_768, 16_385, 16_384, 65, 64, 1):
+        state = torch.empty((6, C), dtype=torch.float64, device="cuda")
+        accepts = torch.empty(C, dtype=torch.int64, device="cuda")
+        trace = torch.empty((T, C), dtype=torch.int8, device="cuda")
+        la = torch.empty((T, C), dtype=torch.float64, device="cuda")
+        summ = torch.empty(29, dtype=torch.float64, device="cuda")
+        scal = torch.empty(4, dtype=torch.float64, device="cuda")
+        ppl.ppl_mcmc(ppl.PPL_MODEL_POLY, data, C, T, seed, burn_in=burn, state=state, accepts=accepts, n_trace=trace,
+                     log_alpha=la, summaries=summ, scalars=scal)
+        state, accepts, trace, la, summ, scal = (v.cpu().numpy() for v in (state, accepts, trace, la, summ, scal))
+        if ref is None:
+            ref = state, accepts, trace, la
+            # |ll| of the first state (importance sampling's execution c) and of every state and proposal after it
+            lw = torch.empty(C, dtype=torch.float64, device="cuda")
+            ppl.ppl_importance(ppl.PPL_MODEL_POLY, data, C, seed, log_weights=lw)
+            size = np.abs(lw.cpu().numpy()) + np.cumsum(np.abs(la) + 4.0, axis=0)
+        np.testing.assert_array_equal(state, ref[0][:, :C])
+        np.testing.assert_array_equal(accepts, ref[1][:C])
+        np.testing.assert_array_equal(trace, ref[2][:, :C])
+        assert np.all(np.abs(la - ref[3][:, :C]) <= (D + 4) * 2.0 ** -52 * size[:, :C])
+        kept = trace[burn:]
+        counts = [(kept == m).sum() for m in range(2, 6)]
+        assert scal[1] == sum(counts) and scal[2] == C and abs(scal[0] - accepts.mean() / T) < 1e-15 * T * C
+        for m in range(4):
+            assert abs(summ[m] - (counts[m] / max(1, sum(counts)))) < 1e-12
+        if n_lo == 2:
+            assert np.allclose(summ[24:], sum(summ[m] * summ[4 + 5 * m:9 + 5 * m] for m in range(4)), rtol=1e-9, atol=1e-9)
