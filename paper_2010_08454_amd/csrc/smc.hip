@@ -115,23 +115,27 @@ constexpr size_t kCkptHeader = 256;
 // device-scope release writes back the L2 of the issuing XCD, which at 256
 // workgroups costs more than the exchange itself).  Two buffers suffice: a
 // block cannot store record e + 2 before every block has stored record e + 1,
-// which each does only after reading all records e.  Returns false
-// (uniformly in the block) once any block has aborted.
+// which each does only after reading all records e.  In two parts: what
+// runs between them overlaps the records' way to the other blocks.
 template <int NW>
-__device__ __forceinline__ bool tagged_barrier(uint64_t *rec, unsigned *bar, unsigned epoch, int nb,
-                                               const uint32_t (&w)[NW], uint32_t (&r)[NW]) {
+__device__ __forceinline__ void tagged_post(uint64_t *rec, unsigned epoch, int nb, const uint32_t (&w)[NW]) {
     static_assert(NW <= kRecWords, "record line overflow");
-    __shared__ int s_bad;
-    unsigned *abort_flag = bar + 1;
-    uint64_t *buf = rec + (size_t)(epoch & 1u) * nb * kRecWords;
-    const uint64_t tag = (uint64_t)epoch << 32;
-    if (threadIdx.x == 0) s_bad = 0;
-    __syncthreads();
     if (threadIdx.x == 0) {
-        uint64_t *mine = buf + (size_t)blockIdx.x * kRecWords;
+        uint64_t *mine = rec + ((size_t)(epoch & 1u) * nb + blockIdx.x) * kRecWords;
+        const uint64_t tag = (uint64_t)epoch << 32;
 #pragma unroll
         for (int k = 0; k < NW; ++k) __hip_atomic_store(mine + k, tag | w[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
+}
+
+// Returns false (uniformly in the block) once any block has aborted.
+template <int NW>
+__device__ __forceinline__ bool tagged_wait(uint64_t *rec, unsigned *bar, unsigned epoch, int nb, uint32_t (&r)[NW]) {
+    __shared__ int s_bad;
+    unsigned *abort_flag = bar + 1;
+    uint64_t *buf = rec + (size_t)(epoch & 1u) * nb * kRecWords;
+    if (threadIdx.x == 0) s_bad = 0;
+    __syncthreads();
 #pragma unroll
     for (int k = 0; k < NW; ++k) r[k] = 0;
     if (threadIdx.x < nb) {          // nb <= kSmcThreads
@@ -169,6 +173,14 @@ __device__ __forceinline__ bool tagged_barrier(uint64_t *rec, unsigned *bar, uns
     return s_bad == 0;
 }
 
+// Both parts, nothing between.
+template <int NW>
+__device__ __forceinline__ bool tagged_barrier(uint64_t *rec, unsigned *bar, unsigned epoch, int nb,
+                                               const uint32_t (&w)[NW], uint32_t (&r)[NW]) {
+    tagged_post<NW>(rec, epoch, nb, w);
+    return tagged_wait<NW>(rec, bar, epoch, nb, r);
+}
+
 __device__ __forceinline__ uint32_t hi32(double v) { return (uint32_t)((uint64_t)__double_as_longlong(v) >> 32); }
 __device__ __forceinline__ uint32_t lo32(double v) { return (uint32_t)(uint64_t)__double_as_longlong(v); }
 __device__ __forceinline__ double from32(uint32_t hi, uint32_t lo) {
@@ -189,16 +201,17 @@ struct Lgssm {
         }
         st[0] = x;
     }
+    static constexpr bool kNoise = true;
     // Noise of slot j at factor s is normal (s mod 4) of block (j, 0, s div 4):
-    // the first or second Box-Muller pair of the block, recomputed at every
-    // factor (keeping the block's four normals across factors costs four
-    // registers per particle, and the kernel would spill).
-    __device__ static float step(const SmcDev &a, int64_t s, uint32_t j, float st[NF], float ys) {
+    // for an even s, z0 is factor s's and z1 factor s + 1's (one Box-Muller pair).
+    // It depends on nothing else, so it is drawn every other factor while the
+    // factor's records are on their way between the blocks.
+    __device__ static void noise(const SmcDev &a, int64_t s, uint32_t j, float &z0, float &z1) {
         const uint4 w = philox(j, 0, (uint32_t)(s >> 2), (a.inst << 8) | kTagPrior, a.key);
-        float z0, z1;
-        if (s & 2) box_muller(unit_f32(w.z), unit_f32(w.w), z0, z1);
-        else box_muller(unit_f32(w.x), unit_f32(w.y), z0, z1);
-        const float x = fmaf(a.hyp[0], st[0], a.hyp[1] * ((s & 1) ? z1 : z0));
+        box_muller(unit_f32((s & 2) ? w.z : w.x), unit_f32((s & 2) ? w.w : w.y), z0, z1);
+    }
+    __device__ static float step(const SmcDev &a, float z, float st[NF], float ys) {
+        const float x = fmaf(a.hyp[0], st[0], a.hyp[1] * z);
         st[0] = x;
         const float r = (ys - x) / a.hyp[2];
         return (float)a.lconst - 0.5f * r * r;
@@ -208,6 +221,8 @@ struct Lgssm {
 template <int K>
 struct Gmm {
     static constexpr int NF = 2 * K;
+    static constexpr bool kNoise = false;
+    __device__ static void noise(const SmcDev &, int64_t, uint32_t, float &, float &) {}
     // hyp = {mu_sd, comp_sd}; state = {log pi_0..K-1, mu_0..K-1}
     __device__ static void init(const SmcDev &a, uint32_t j, float st[NF]) {
         const uint32_t c3 = (a.inst << 8) | kTagPrior;
@@ -227,7 +242,7 @@ struct Gmm {
 #pragma unroll
         for (int k = 0; k < K; ++k) st[K + k] = a.hyp[0] * z[k];
     }
-    __device__ static float step(const SmcDev &a, int64_t, uint32_t, float st[NF], float ys) {
+    __device__ static float step(const SmcDev &a, float, float st[NF], float ys) {
         const float inv = 1.0f / a.hyp[1];
         float t[K], mx = -INFINITY;
 #pragma unroll
@@ -263,7 +278,7 @@ __device__ double gmm_loglik_upto(const SmcDev &a, int64_t s, const float st[2 *
     float blk = 0.0f;
     int c = 0;
     for (int64_t d = 0; d <= s; ++d) {
-        blk += Gmm<K>::step(a, d, 0, const_cast<float *>(st), a.y[d]);
+        blk += Gmm<K>::step(a, 0.0f, const_cast<float *>(st), a.y[d]);
         if (++c == 16) {
             tot += (double)blk;
             blk = 0.0f;
@@ -607,6 +622,11 @@ __global__ __launch_bounds__(kSmcThreads) void smc_persistent_kernel(SmcDev a) {
         }
     }
 
+    float zn[M::kNoise ? P : 1][2];          // the factor pair's noise
+    if constexpr (M::kNoise) {
+#pragma unroll
+        for (int p = 0; p < P; ++p) M::noise(a, a.t0 & ~(int64_t)1, (uint32_t)(base + p), zn[p][0], zn[p][1]);
+    }
     for (int64_t s = a.t0; status == 0 && s < a.t1; ++s) {
         if (s == a.t0 || (s % kYChunk) == 0) {     // stage the chunk of observations holding factor s
             const int64_t c0 = s - s % kYChunk;
@@ -622,7 +642,7 @@ __global__ __launch_bounds__(kSmcThreads) void smc_persistent_kernel(SmcDev a) {
         asm volatile("" : "+v"(jb));
 #pragma unroll
         for (int p = 0; p < P; ++p) {
-            const float f = M::step(a, s, (uint32_t)(jb + p), st[p], ys);
+            const float f = M::step(a, M::kNoise ? ((s & 1) ? zn[M::kNoise ? p : 0][1] : zn[M::kNoise ? p : 0][0]) : 0.0f, st[p], ys);
             if (valid[p]) kahan_add(lw[p], lwc[p], f);
         }
         // block partial for the ESS trigger
@@ -642,8 +662,14 @@ __global__ __launch_bounds__(kSmcThreads) void smc_persistent_kernel(SmcDev a) {
         double s1b = s1l, s2b = s2l;
         block_sum2_f64(s1b, s2b, ldsd);
         uint32_t rt[5];
-        if (!tagged_barrier<5>(a.rec, a.bar, ++epoch, nb,
-                               {__float_as_uint(mb), hi32(s1b), lo32(s1b), hi32(s2b), lo32(s2b)}, rt)) {
+        tagged_post<5>(a.rec, ++epoch, nb, {__float_as_uint(mb), hi32(s1b), lo32(s1b), hi32(s2b), lo32(s2b)});
+        if constexpr (M::kNoise) {
+            if ((s & 1) && s + 1 < a.t1) {
+#pragma unroll
+                for (int p = 0; p < P; ++p) M::noise(a, s + 1, (uint32_t)(jb + p), zn[p][0], zn[p][1]);
+            }
+        }
+        if (!tagged_wait<5>(a.rec, a.bar, epoch, nb, rt)) {
             alive = false;
             break;
         }
