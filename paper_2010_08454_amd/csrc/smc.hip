@@ -12,6 +12,20 @@
 // resampling variables and the FP64 normaliser calls fit without spilling
 // (spilled registers would be written back and refetched through HBM at
 // every grid barrier).
+//
+// What bounds it is the chain of a factor, not arithmetic: at N = 2^20 (256 blocks
+// of 8 particles per thread) the 1000 factors and 715 events of the state-space
+// model hold 1715 exchanges of about 6 us, each a store that has to reach the
+// others' caches and a poll that has to come back, and the rest is work of the
+// two waves per SIMD between exchanges.  So the chain is kept short: records are
+// merged from LDS by all waves with one workgroup barrier, a tile's totals leave
+// before its prefix sums and state do, noise and log Z-hat are worked on while
+// records travel, and a particle marks its slots instead of every slot searching
+// (8 slots per thread: 6.6 us of search and 1.3 us of staging per event).
+// Measured against merging by one wave, serial polls and a search per slot:
+// 1000 x 2^20 30.1 -> 21.8 ms, 300 x 1000 3.30 -> 2.03 ms, 300 x 100003 4.55 ->
+// 3.34 ms, mixture 300 x 20011 with K = 4 1.35 -> 1.26 ms; the noise drawn
+// while records travel is 3.2 ms of the first.
 // Per factor s:
 //   1. every particle advances to factor s and adds its log-factor (FP32,
 //      compensated summation);
@@ -21,10 +35,10 @@
 //   3. if ESS < ess_frac N (and s is not the last factor): FP64 weights
 //      e = exp(lw - max) give the epoch normaliser and the quantised integer
 //      weights q; each block scans its q and publishes its tile total, its
-//      tile-local exclusive prefix sums and its particles' state; grid barrier; each
-//      block finds the contiguous ancestor range of its slots, stages those
-//      prefix sums in LDS, and every slot binary-searches its ancestor there
-//      and gathers the ancestor's state; lw = 0.
+//      tile-local exclusive prefix sums and its particles' state; grid barrier; every
+//      particle of the few tiles that hold a block's ancestors marks the first slot
+//      it is the ancestor of, a running maximum fills the other slots, and every
+//      slot gathers its ancestor's state; lw = 0.
 // Blocks meet at a record barrier: each block stores its record (the partial
 // of step 2, the tile total of step 3, the final sums) on its own cache line
 // and thread t of every block polls line t, so every block holds every record
@@ -56,7 +70,11 @@ constexpr int kBarWords = kBarLine;           // word 1: abort flag
 constexpr int kRecWords = 16;                 // 64-bit words per 128-byte record line
 constexpr uint32_t kSpinLimit = 1u << 24;     // polls before a wait is declared hung (seconds)
 constexpr int kYChunk = 2048;                 // observations staged in LDS at a time
-constexpr int kStage = 8192;                  // most prefix sums staged in LDS for the ancestor search
+// Most tiles whose particles mark a block's slots.  At even weights a block's ancestors
+// lie in its own and one or two neighbouring tiles; five tiles of marks cost about
+// what the search in memory costs, which is left to ancestors that are strewn wider.
+constexpr int kScatterTiles = 5;
+constexpr int kBatchTries = 64;               // reloads of a batch of tagged words before polling them one by one
 
 struct SmcDev {
     const float *y;
@@ -68,7 +86,7 @@ struct SmcDev {
     float hyp[5];            // model constants (FP32)
     double lconst;           // LGSSM: -1/2 log(2 pi r^2) ; GMM: -1/2 log(2 pi) - log(sd)
     int kbits;               // quantisation exponent
-    int stage_cap;           // prefix sums that fit in the LDS stage
+    uint64_t inv_n;          // floor((2^64 - 1) / N)
     // outputs (may be null)
     double *scalars;
     float *lw_out, *lat_out;
@@ -110,7 +128,7 @@ constexpr size_t kCkptHeader = 256;
 // every block's record): thread 0 stores NW words on its line of buffer
 // e mod 2 with relaxed device-scope stores, each word holding e in its high
 // half and 32 bits of the record in its low half; thread t < nb polls line t
-// (its last word first) until every word of the line holds e.  Each word
+// until every word of the line holds e, and leaves the words in LDS.  Each word
 // validates itself, so the exchange needs no release and no acquire (a
 // device-scope release writes back the L2 of the issuing XCD, which at 256
 // workgroups costs more than the exchange itself).  Two buffers suffice: a
@@ -128,57 +146,47 @@ __device__ __forceinline__ void tagged_post(uint64_t *rec, unsigned epoch, int n
     }
 }
 
-// Returns false (uniformly in the block) once any block has aborted.
+// Every block's record words, by word and block, after tagged_wait.
+struct RecLds {
+    uint32_t w[5][kSmcThreads];
+    int bad;                          // set (never reset) once a wait or a tagged read gave up
+};
+
+// Leaves word k of block t's record in L.w[k][t].  Returns false (uniformly in the
+// block) once any block has aborted.  L.w is free for the next wait after the
+// workgroup barrier that every caller passes in between.
 template <int NW>
-__device__ __forceinline__ bool tagged_wait(uint64_t *rec, unsigned *bar, unsigned epoch, int nb, uint32_t (&r)[NW]) {
-    __shared__ int s_bad;
+__device__ __forceinline__ bool tagged_wait(uint64_t *rec, unsigned *bar, unsigned epoch, int nb, RecLds &L) {
+    static_assert(NW <= 5, "record words in LDS");
     unsigned *abort_flag = bar + 1;
-    uint64_t *buf = rec + (size_t)(epoch & 1u) * nb * kRecWords;
-    if (threadIdx.x == 0) s_bad = 0;
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < NW; ++k) r[k] = 0;
     if (threadIdx.x < nb) {          // nb <= kSmcThreads
-        uint64_t *line = buf + (size_t)threadIdx.x * kRecWords;
+        uint64_t *line = rec + ((size_t)(epoch & 1u) * nb + threadIdx.x) * kRecWords;
         uint32_t spins = 0;
         while (true) {
-            const uint64_t last = __hip_atomic_load(line + NW - 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if ((last >> 32) == (uint64_t)epoch) {
-                uint64_t v[NW];
-                bool all = true;
+            uint64_t v[NW];
+            bool all = true;
 #pragma unroll
-                for (int k = 0; k < NW - 1; ++k) {
-                    v[k] = __hip_atomic_load(line + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    all = all && (v[k] >> 32) == (uint64_t)epoch;
-                }
-                v[NW - 1] = last;
-                if (all) {
+            for (int k = 0; k < NW; ++k) v[k] = __hip_atomic_load(line + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
-                    for (int k = 0; k < NW; ++k) r[k] = (uint32_t)v[k];
-                    break;
-                }
+            for (int k = 0; k < NW; ++k) all = all && (v[k] >> 32) == (uint64_t)epoch;
+            if (all) {
+#pragma unroll
+                for (int k = 0; k < NW; ++k) L.w[k][threadIdx.x] = (uint32_t)v[k];
+                break;
             }
             __builtin_amdgcn_s_sleep(1);
             if ((++spins & 63) == 0) {
-                if (__hip_atomic_load(abort_flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) { s_bad = 1; break; }
+                if (__hip_atomic_load(abort_flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) { L.bad = 1; break; }
                 if (spins > kSpinLimit) {
                     __hip_atomic_store(abort_flag, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    s_bad = 1;
+                    L.bad = 1;
                     break;
                 }
             }
         }
     }
     __syncthreads();
-    return s_bad == 0;
-}
-
-// Both parts, nothing between.
-template <int NW>
-__device__ __forceinline__ bool tagged_barrier(uint64_t *rec, unsigned *bar, unsigned epoch, int nb,
-                                               const uint32_t (&w)[NW], uint32_t (&r)[NW]) {
-    tagged_post<NW>(rec, epoch, nb, w);
-    return tagged_wait<NW>(rec, bar, epoch, nb, r);
+    return L.bad == 0;
 }
 
 __device__ __forceinline__ uint32_t hi32(double v) { return (uint32_t)((uint64_t)__double_as_longlong(v) >> 32); }
@@ -368,28 +376,6 @@ __device__ __noinline__ double log_f64(double v) { return log(v); }
 __device__ __noinline__ double exp_f64(double v) { return exp(v); }
 
 // ------------------------------------------------------ block helpers --
-__device__ __forceinline__ float block_max_f32(float v, float *lds) {
-    v = wave_max_dpp(v);
-    if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = v;
-    __syncthreads();
-    float m = lds[0];
-#pragma unroll
-    for (int w = 1; w < kSmcWaves; ++w) m = fmaxf(m, lds[w]);
-    __syncthreads();
-    return m;
-}
-
-__device__ __forceinline__ double block_sum_f64(double v, double *lds) {
-    v = wave_sum_dpp(v);
-    if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = v;
-    __syncthreads();
-    double s = 0.0;
-#pragma unroll
-    for (int w = 0; w < kSmcWaves; ++w) s += lds[w];
-    __syncthreads();
-    return s;
-}
-
 // Two sums in one pass (lds holds 2 * kSmcWaves doubles).
 __device__ __forceinline__ void block_sum2_f64(double &u, double &v, double *lds) {
     u = wave_sum_dpp(u);
@@ -410,46 +396,87 @@ __device__ __forceinline__ void block_sum2_f64(double &u, double &v, double *lds
     v = b;
 }
 
-// Exclusive scan of one u64 per thread across the block; returns the prefix,
-// writes the block total.
-__device__ __forceinline__ uint64_t block_exclusive_scan_u64(uint64_t v, uint64_t *lds, uint64_t &total) {
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    uint64_t incl = v;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint64_t t = __shfl_up(incl, o, 64);
-        if (lane >= o) incl += t;
-    }
-    if (lane == 63) lds[wv] = incl;
-    __syncthreads();
-    uint64_t off = 0, tot = 0;
-#pragma unroll
-    for (int w = 0; w < kSmcWaves; ++w) {
-        const uint64_t x = lds[w];
-        if (w < wv) off += x;
-        tot += x;
-    }
-    __syncthreads();
-    total = tot;
-    return off + incl - v;
+// Inclusive scan of one u64 per lane: four row shifts and two row broadcasts
+// (DPP; lanes that a step leaves out add 0).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint64_t dpp_u64(uint64_t v) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, CTRL, ROWS, 0xF, false);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(v >> 32), CTRL, ROWS, 0xF, false);
+    return ((uint64_t)hi << 32) | lo;
+}
+__device__ __forceinline__ uint64_t wave_scan_u64(uint64_t v) {
+    v += dpp_u64<0x111, 0xF>(v);     // row_shr 1, 2, 4, 8: inclusive within each row of 16
+    v += dpp_u64<0x112, 0xF>(v);
+    v += dpp_u64<0x114, 0xF>(v);
+    v += dpp_u64<0x118, 0xF>(v);
+    v += dpp_u64<0x142, 0xA>(v);     // row 0's total into row 1, row 2's into row 3
+    v += dpp_u64<0x143, 0xC>(v);     // rows 0 and 1's total into rows 2 and 3
+    return v;
 }
 
-// Merge of the per-block partials {m, s1, s2} (identical in every block):
-// fixed order, FP32 rescale factors (this feeds the resampling trigger only).
-// Merges the per-block partials {max, s1, s2} that thread t < nb holds for
-// block t, in the same order in every block.
-__device__ __forceinline__ void merge_partials(float mb, double p1, double p2, float *ldsf, double *ldsd, float &M,
-                                               double &S1, double &S2) {
-    M = block_max_f32(mb, ldsf);
-    double s1 = 0.0, s2 = 0.0;
-    if (M > -INFINITY && mb > -INFINITY) {
-        const float c = expf(mb - M);
-        s1 = p1 * (double)c;
-        s2 = p2 * (double)(c * c);
+// Maximum and inclusive running maximum of one u32 per lane, the same steps.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_u32(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xF, false);
+}
+__device__ __forceinline__ uint32_t wave_scan_max_u32(uint32_t v) {
+    v = max(v, dpp_u32<0x111, 0xF>(v));
+    v = max(v, dpp_u32<0x112, 0xF>(v));
+    v = max(v, dpp_u32<0x114, 0xF>(v));
+    v = max(v, dpp_u32<0x118, 0xF>(v));
+    v = max(v, dpp_u32<0x142, 0xA>(v));
+    v = max(v, dpp_u32<0x143, 0xC>(v));
+    return v;
+}
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_readlane((int)wave_scan_max_u32(v), 63);
+}
+
+// Position of entry i in the LDS arrays that a thread reads or writes P = 8
+// consecutive entries of: one word of padding per eight, so that the lanes'
+// eight-word strides fall on different banks.
+__device__ __forceinline__ int padded(int i) { return i + (i >> 3); }
+constexpr int64_t padded_size(int64_t n) { return n + (n + 7) / 8; }
+
+constexpr int kRecGroups = kSmcThreads / 64;     // groups of 64 records, at most one per wave
+
+// Merges the per-block partials {max, s1, s2} (FP32 rescale factors: this feeds the
+// resampling trigger only), in the same order in every block: every wave takes
+// the maximum over all records for itself, wave g sums records 64 g .. 64 g + 63,
+// and after one workgroup barrier every thread adds the groups in order.
+__device__ __forceinline__ void merge_partials(const RecLds &L, int nb, double *lds, float &M, double &S1, double &S2) {
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    float mx = -INFINITY;
+#pragma unroll
+    for (int g = 0; g < kRecGroups; ++g)
+        if (64 * g < nb && 64 * g + lane < nb) mx = fmaxf(mx, __uint_as_float(L.w[0][64 * g + lane]));
+    M = wave_max_dpp(mx);
+    if (64 * wv < nb) {
+        const int t = 64 * wv + lane;
+        const float mb = t < nb ? __uint_as_float(L.w[0][t]) : -INFINITY;
+        double s1 = 0.0, s2 = 0.0;
+        if (M > -INFINITY && mb > -INFINITY) {
+            const float c = expf(mb - M);
+            s1 = from32(L.w[1][t], L.w[2][t]) * (double)c;
+            s2 = from32(L.w[3][t], L.w[4][t]) * (double)(c * c);
+        }
+        s1 = wave_sum_dpp(s1);
+        s2 = wave_sum_dpp(s2);
+        if (lane == 0) {
+            lds[wv] = s1;
+            lds[kRecGroups + wv] = s2;
+        }
     }
-    block_sum2_f64(s1, s2, ldsd);
-    S1 = s1;
-    S2 = s2;
+    __syncthreads();
+    S1 = 0.0;
+    S2 = 0.0;
+#pragma unroll
+    for (int g = 0; g < kRecGroups; ++g) {
+        if (64 * g < nb) {
+            S1 += lds[g];
+            S2 += lds[kRecGroups + g];
+        }
+    }
 }
 
 // Slot thresholds.  For integers, N Q_a > j S + U  <=>  Q_a > floor((j S + U) / N),
@@ -461,9 +488,23 @@ struct SlotThreshold {
     uint64_t quo, rem;   // of (j Sr + U) / N
 };
 
-__device__ __forceinline__ SlotThreshold slot_threshold(uint32_t j, uint64_t Sr, uint64_t U, uint64_t N) {
-    const uint64_t num = (uint64_t)j * Sr + U;
-    return SlotThreshold{num / N, num % N};
+// num / N and the remainder with inv = floor((2^64 - 1) / N): the high half of
+// num inv is at most two short of the quotient.
+__device__ __forceinline__ SlotThreshold divide_n(uint64_t num, uint64_t N, uint64_t inv) {
+    SlotThreshold t;
+    t.quo = __umul64hi(num, inv);
+    t.rem = num - t.quo * N;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const bool more = t.rem >= N;
+        t.rem = more ? t.rem - N : t.rem;
+        t.quo = more ? t.quo + 1 : t.quo;
+    }
+    return t;
+}
+
+__device__ __forceinline__ SlotThreshold slot_threshold(uint32_t j, uint64_t Sr, uint64_t U, uint64_t N, uint64_t inv) {
+    return divide_n((uint64_t)j * Sr + U, N, inv);
 }
 
 __device__ __forceinline__ void slot_threshold_next(SlotThreshold &t, uint64_t Sr, uint64_t N) {
@@ -555,31 +596,30 @@ __device__ __forceinline__ int find_ancestor_global(uint64_t tau, int64_t N, int
 // registers never add to the plain filter's).
 template <class M, int P, bool MOVES>
 __global__ __launch_bounds__(kSmcThreads) void smc_persistent_kernel(SmcDev a) {
-    __shared__ float ldsf[kSmcWaves];
+    __shared__ float s_max[kSmcWaves];
     __shared__ double ldsd[2 * kSmcWaves];
-    __shared__ uint64_t ldsu[kSmcWaves];
+    __shared__ uint64_t s_scan[kSmcWaves];
+    __shared__ double s_esum[kSmcWaves];
     __shared__ float ybuf[kYChunk];
-    __shared__ int s_rng[2];
-    __shared__ int s_cnt[kSmcWaves];
-    // dynamic LDS: tile_end[nb] | tile_pre[nb] | stage[stage_cap] | own_q[kTile] (u64) |
-    // s_anc[kTile] (i32) | own_x[kTile] (FP32, one-field models only)
+    __shared__ uint32_t s_cnt[kSmcWaves];
+    __shared__ double s_merge[2 * kRecGroups];
+    __shared__ RecLds L;
+    // dynamic LDS: tile_end[nb] | tile_pre[nb] | own_q[kTile] (u64) | s_slot[kTile] (i32) |
+    // own_x[kTile] (FP32, one-field models only); the last three with padded() positions
     constexpr int kTile = kSmcThreads * P;
+    constexpr int kTilePad = (int)padded_size(kTile);
     constexpr bool kOwnX = M::NF == 1;
     extern __shared__ uint64_t dyn[];
     const int nb = gridDim.x;
     uint64_t *tile_end = dyn;
     uint64_t *tile_pre = dyn + nb;
-    uint64_t *stage = dyn + 2 * nb;
-    uint64_t *own_q = dyn + 2 * nb + a.stage_cap;
-    int32_t *s_anc = (int32_t *)(own_q + kTile);
-    float *own_x = (float *)(s_anc + kTile);
+    uint64_t *own_q = dyn + 2 * nb;
+    int32_t *s_slot = (int32_t *)(own_q + kTilePad);
+    float *own_x = (float *)(s_slot + kTilePad);
 
     const int64_t N = a.N;
     const int64_t tile0 = (int64_t)blockIdx.x * kTile;                 // this block's first slot
     const int tlen = (int)min((int64_t)kTile, N - tile0);               // and its slot count
-    // tagged prefix words loaded per round: all of them for the one-field model,
-    // fewer beside a larger particle state
-    constexpr int kLoadBatch = M::NF > 2 ? 4 : 16;
     const int64_t base = (int64_t)blockIdx.x * kTile + (int64_t)threadIdx.x * P;
 
     float st[P][M::NF];
@@ -622,6 +662,25 @@ __global__ __launch_bounds__(kSmcThreads) void smc_persistent_kernel(SmcDev a) {
         }
     }
 
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    // Bookkeeping is the last wave's: it neither posts nor (up to 256 blocks) polls.
+    // The normaliser of the last resampling is added to log Z-hat there while the
+    // next factor's records are on their way.
+    constexpr int kBook = kSmcThreads - 64;
+    const bool book = threadIdx.x == kBook;
+    double pend = 0.0;
+    float pend_m = 0.0f;
+    int64_t pend_s = -1;
+    auto flush = [&]() {
+        if (wv == kSmcWaves - 1 && pend_s >= 0) {
+            const double inc = (double)pend_m + log_f64(pend) - logN;
+            logz += inc;
+            if (a.logz_tr && blockIdx.x == 0 && book) a.logz_tr[pend_s] = inc;
+        }
+        pend_s = -1;
+    };
+    if (threadIdx.x == 0) L.bad = 0;
+    __syncthreads();
     float zn[M::kNoise ? P : 1][2];          // the factor pair's noise
     if constexpr (M::kNoise) {
 #pragma unroll
@@ -649,7 +708,15 @@ __global__ __launch_bounds__(kSmcThreads) void smc_persistent_kernel(SmcDev a) {
         float ml = -INFINITY;
 #pragma unroll
         for (int p = 0; p < P; ++p) ml = fmaxf(ml, lw[p]);
-        const float mb = block_max_f32(ml, ldsf);
+        // Workgroup barriers of a factor: after the wave maxima, after the wave
+        // sums, and the one of tagged_wait; every LDS word written between two of
+        // them is next written after another two.
+        ml = wave_max_dpp(ml);
+        if (lane == 0) s_max[wv] = ml;
+        __syncthreads();
+        float mb = s_max[0];
+#pragma unroll
+        for (int w = 1; w < kSmcWaves; ++w) mb = fmaxf(mb, s_max[w]);
         float s1l = 0.0f, s2l = 0.0f;
         if (mb > -INFINITY) {
 #pragma unroll
@@ -659,30 +726,44 @@ __global__ __launch_bounds__(kSmcThreads) void smc_persistent_kernel(SmcDev a) {
                 s2l = fmaf(e, e, s2l);
             }
         }
-        double s1b = s1l, s2b = s2l;
-        block_sum2_f64(s1b, s2b, ldsd);
-        uint32_t rt[5];
-        tagged_post<5>(a.rec, ++epoch, nb, {__float_as_uint(mb), hi32(s1b), lo32(s1b), hi32(s2b), lo32(s2b)});
+        {
+            const double u = wave_sum_dpp((double)s1l), v = wave_sum_dpp((double)s2l);
+            if (lane == 0) {
+                ldsd[wv] = u;
+                ldsd[kSmcWaves + wv] = v;
+            }
+        }
+        __syncthreads();
+        ++epoch;
+        if (threadIdx.x == 0) {
+            double s1b = 0.0, s2b = 0.0;
+#pragma unroll
+            for (int w = 0; w < kSmcWaves; ++w) {
+                s1b += ldsd[w];
+                s2b += ldsd[kSmcWaves + w];
+            }
+            tagged_post<5>(a.rec, epoch, nb, {__float_as_uint(mb), hi32(s1b), lo32(s1b), hi32(s2b), lo32(s2b)});
+        }
+        flush();
         if constexpr (M::kNoise) {
             if ((s & 1) && s + 1 < a.t1) {
 #pragma unroll
                 for (int p = 0; p < P; ++p) M::noise(a, s + 1, (uint32_t)(jb + p), zn[p][0], zn[p][1]);
             }
         }
-        if (!tagged_wait<5>(a.rec, a.bar, epoch, nb, rt)) {
+        if (!tagged_wait<5>(a.rec, a.bar, epoch, nb, L)) {
             alive = false;
             break;
         }
         float Mg;
         double S1, S2;
-        merge_partials(threadIdx.x < nb ? __uint_as_float(rt[0]) : -INFINITY, from32(rt[1], rt[2]),
-                       from32(rt[3], rt[4]), ldsf, ldsd, Mg, S1, S2);
+        merge_partials(L, nb, s_merge, Mg, S1, S2);
         Mlast = Mg;
         if (!(Mg > -INFINITY)) { status = PPL_E_ZERO_WEIGHT; break; }
         if (!(S1 > 0.0) || isnan(S1) || isnan(S2)) { status = PPL_E_NONFINITE; break; }
         const double ess = S1 * S1 / S2;
         const bool res = (s < a.T - 1) && (ess < (double)a.ess_frac * (double)N);
-        if (blockIdx.x == 0 && threadIdx.x == 0) {
+        if (blockIdx.x == 0 && book) {
             if (a.ess_trace) a.ess_trace[s] = ess;
             if (a.resampled) a.resampled[s] = res ? 1 : 0;
             if (a.logz_tr && !res) a.logz_tr[s] = 0.0;
@@ -705,9 +786,32 @@ __global__ __launch_bounds__(kSmcThreads) void smc_persistent_kernel(SmcDev a) {
             qx[p] = run;
             run += (uint64_t)floor(ldexp(e, a.kbits));
         }
-        uint64_t btot;
-        const uint64_t off = block_exclusive_scan_u64(run, ldsu, btot);
-        const double eb = block_sum_f64(esl, ldsd);
+        const uint64_t incl = wave_scan_u64(run);
+        {
+            const double e = wave_sum_dpp(esl);
+            if (lane == 63) {
+                s_scan[wv] = incl;
+                s_esum[wv] = e;
+            }
+        }
+        __syncthreads();
+        uint64_t off = incl - run;
+#pragma unroll
+        for (int w = 0; w < kSmcWaves; ++w)
+            if (w < wv) off += s_scan[w];
+        // The totals leave first; the tile itself is published while they are on
+        // their way (a reader that is early finds an old tag and loads again).
+        ++epoch;
+        if (threadIdx.x == 0) {
+            uint64_t btot = 0;
+            double eb = 0.0;
+#pragma unroll
+            for (int w = 0; w < kSmcWaves; ++w) {
+                btot += s_scan[w];
+                eb += s_esum[w];
+            }
+            tagged_post<4>(a.rec, epoch, nb, {(uint32_t)(btot >> 32), (uint32_t)btot, hi32(eb), lo32(eb)});
+        }
         const uint64_t qtag = qtag_of(nres);
         const uint32_t xtag = (uint32_t)(nres + 1);
         // The tile's prefix sums (and a one-field state) go to LDS, where this
@@ -716,8 +820,8 @@ __global__ __launch_bounds__(kSmcThreads) void smc_persistent_kernel(SmcDev a) {
         // registers would scatter each store over a wave's 64 particles).
 #pragma unroll
         for (int p = 0; p < P; ++p) {
-            own_q[threadIdx.x * P + p] = off + qx[p];
-            if constexpr (kOwnX) own_x[threadIdx.x * P + p] = st[p][0];
+            own_q[padded(threadIdx.x * P + p)] = off + qx[p];
+            if constexpr (kOwnX) own_x[padded(threadIdx.x * P + p)] = st[p][0];
         }
         if constexpr (!kOwnX) {
 #pragma unroll
@@ -733,218 +837,180 @@ __global__ __launch_bounds__(kSmcThreads) void smc_persistent_kernel(SmcDev a) {
         }
         __syncthreads();
         for (int i = threadIdx.x; i < tlen; i += kSmcThreads) {
-            __hip_atomic_store(a.qtag + tile0 + i, qtag | own_q[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(a.qtag + tile0 + i, qtag | own_q[padded(i)], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if constexpr (kOwnX)
-                __hip_atomic_store(a.xtag + tile0 + i, ((uint64_t)xtag << 32) | __float_as_uint(own_x[i]),
+                __hip_atomic_store(a.xtag + tile0 + i, ((uint64_t)xtag << 32) | __float_as_uint(own_x[padded(i)]),
                                    __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
-        uint32_t rq[4];
-        if (!tagged_barrier<4>(a.rec, a.bar, ++epoch, nb,
-                               {(uint32_t)(btot >> 32), (uint32_t)btot, hi32(eb), lo32(eb)}, rq)) {
+        for (int i = threadIdx.x; i < kTilePad; i += kSmcThreads) s_slot[i] = 0;
+        const uint4 rw = philox(0, 0, (uint32_t)s, (a.inst << 8) | kTagResample, a.key);
+        if (!tagged_wait<4>(a.rec, a.bar, epoch, nb, L)) {
             alive = false;
             break;
         }
         unsigned *abort_flag = a.bar + 1;
         bool bad = false;
 
-        // tile prefixes (LDS) and the normaliser sum, in the same order in every block
+        // Tile prefixes and the normaliser sum, in the same order in every block:
+        // every wave scans the records for itself (no workgroup barrier).
+        int anc[P];
         {
-            const uint64_t v = threadIdx.x < nb ? ((uint64_t)rq[0] << 32) | rq[1] : 0;
-            const double ev0 = threadIdx.x < nb ? from32(rq[2], rq[3]) : 0.0;
-            uint64_t S;
-            const uint64_t ex = block_exclusive_scan_u64(v, ldsu, S);
-            if (threadIdx.x < nb) {
-                tile_pre[threadIdx.x] = ex;
-                tile_end[threadIdx.x] = ex + v;
+            uint64_t tend[kRecGroups], S = 0;    // inclusive prefix of this lane's tiles
+            double ev = 0.0;
+#pragma unroll
+            for (int g = 0; g < kRecGroups; ++g) {
+                tend[g] = ~0ull;
+                if (64 * g < nb) {
+                    const int t = 64 * g + lane;
+                    const uint64_t v = t < nb ? ((uint64_t)L.w[0][t] << 32) | L.w[1][t] : 0;
+                    const uint64_t in = S + wave_scan_u64(v);
+                    if (t < nb) {
+                        tend[g] = in;
+                        if (wv == 0) {
+                            tile_pre[t] = in - v;
+                            tile_end[t] = in;
+                        }
+                    }
+                    S = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(in >> 32), 63) << 32) |
+                        (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)in, 63);
+                    if (wv == kSmcWaves - 1) ev += wave_sum_dpp(t < nb ? from32(L.w[2][t], L.w[3][t]) : 0.0);
+                }
             }
-            const double ev = block_sum_f64(ev0, ldsd);     // contains the barrier for tile_*
-            const uint4 rw = philox(0, 0, (uint32_t)s, (a.inst << 8) | kTagResample, a.key);
+            pend = ev;
+            pend_m = Mg;
+            pend_s = s;
             const uint64_t U = __umul64hi(((uint64_t)rw.y << 32) | rw.x, S);
-            const double inc = (double)Mg + log_f64(ev) - logN;
-            logz += inc;
-            if (a.logz_tr && blockIdx.x == 0 && threadIdx.x == 0) a.logz_tr[s] = inc;
             ++nres;
             const uint64_t NN = (uint64_t)N;
-            const uint64_t Sq = S / NN, Sr = S - Sq * NN;
+            const SlotThreshold sn = divide_n(S, NN, a.inv_n);
+            const uint64_t Sq = sn.quo, Sr = sn.rem;
 
-            // ancestor range of this block's slots: the first and last slot's
-            // ancestors, each found by half of the block.  The ancestor's tile
-            // is the first with tile_end > tau (LDS); within it the exclusive
-            // prefix sums are non-decreasing and the first is <= tau, so the
-            // ancestor's offset is the number of entries <= tau, less one,
-            // counted with one round of independent loads.
+            // Tiles of the ancestors of this block's first and last slot: the
+            // first whose end exceeds the slot's threshold, counted over the lanes'
+            // tiles.
             const int js0 = blockIdx.x * kTile;
             const int js1 = (int)min((int64_t)js0 + kTile, N) - 1;
-            {
-                constexpr int kHalf = kSmcThreads / 2;
-                const int half = threadIdx.x / kHalf, hl = threadIdx.x % kHalf;
-                const uint32_t jsx = (uint32_t)(half ? js1 : js0);
-                const SlotThreshold t = slot_threshold(jsx, Sr, U, NN);
-                const uint64_t tau = (uint64_t)jsx * Sq + t.quo;
-                int lo = 0, hi = nb - 1;
-                while (lo < hi) {
-                    const int mid = (lo + hi) >> 1;
-                    if (tile_end[mid] > tau) hi = mid; else lo = mid + 1;
-                }
-                const int64_t tb = (int64_t)lo * kTile;
-                const int len = (int)min((int64_t)kTile, N - tb);
-                const uint64_t pre = tile_pre[lo];
-                // all loads first (clamped in range), then the count; a word that
-                // is not yet current sends the thread through the polling reads
-                constexpr int kPer = kTile / kHalf;
-                int cnt = 0;
-                bool fresh = !a.poll_all;
-                if (lo == (int)blockIdx.x) {       // this block's own tile: its prefix sums are in LDS
-                    for (int i = hl; i < len; i += kHalf) cnt += (pre + own_q[i] <= tau) ? 1 : 0;
-                } else {
+            auto tile_of = [&](int j) {
+                const uint64_t tau = (uint64_t)j * Sq + slot_threshold((uint32_t)j, Sr, U, NN, a.inv_n).quo;
+                int t = 0;
 #pragma unroll
-                for (int k0 = 0; k0 < kPer; k0 += kLoadBatch) {
-                    uint64_t v[kLoadBatch];
-#pragma unroll
-                    for (int k = 0; k < kLoadBatch; ++k)
-                        v[k] = __hip_atomic_load(a.qtag + tb + min(hl + (k0 + k) * kHalf, len - 1), __ATOMIC_RELAXED,
-                                                 __HIP_MEMORY_SCOPE_AGENT);
-#pragma unroll
-                    for (int k = 0; k < kLoadBatch; ++k) {
-                        if (k0 + k < kPer && hl + (k0 + k) * kHalf < len) {
-                            fresh = fresh && (v[k] & ~kQMask) == qtag;
-                            cnt += (pre + (v[k] & kQMask) <= tau) ? 1 : 0;
-                        }
-                    }
-                }
-                }
-                if (!fresh) {
-                    cnt = 0;
-                    for (int i = hl; i < len; i += kHalf)
-                        cnt += (pre + read_q(a.qtag + tb + i, qtag, abort_flag, bad) <= tau) ? 1 : 0;
-                }
-#pragma unroll
-                for (int o = 32; o > 0; o >>= 1) cnt += __shfl_xor(cnt, o, 64);
-                if ((threadIdx.x & 63) == 0) s_cnt[threadIdx.x >> 6] = cnt;
-                __syncthreads();
-                if (hl == 0) {
-                    int c = 0;
-                    for (int w = 0; w < kSmcWaves / 2; ++w) c += s_cnt[half * (kSmcWaves / 2) + w];
-                    s_rng[half] = (int)(tb + c - 1);
-                }
-            }
-            __syncthreads();
-            const int a_lo = s_rng[0], a_hi = s_rng[1];
-            const int span = a_hi - a_lo + 1;
-            const bool staged = span >= 1 && span <= a.stage_cap;
-            if (staged) {
-                constexpr int kPer = kStage / kSmcThreads;
-                bool fresh = !a.poll_all;
-#pragma unroll
-                for (int k0 = 0; k0 < kPer; k0 += kLoadBatch) {
-                    uint64_t v[kLoadBatch];
-#pragma unroll
-                    for (int k = 0; k < kLoadBatch; ++k) {
-                        const int aa = a_lo + min((int)threadIdx.x + (k0 + k) * kSmcThreads, span - 1);
-                        v[k] = (uint64_t)(aa - tile0) < (uint64_t)tlen
-                                   ? qtag | own_q[aa - tile0]
-                                   : __hip_atomic_load(a.qtag + aa, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    }
-#pragma unroll
-                    for (int k = 0; k < kLoadBatch; ++k) {
-                        const int i = threadIdx.x + (k0 + k) * kSmcThreads;
-                        if (k0 + k < kPer && i < span) {
-                            fresh = fresh && (v[k] & ~kQMask) == qtag;
-                            stage[i] = tile_pre[(a_lo + i) / kTile] + (v[k] & kQMask);
-                        }
-                    }
-                }
-                if (!fresh) {
-                    for (int i = threadIdx.x; i < span; i += kSmcThreads) {
-                        const int aa = a_lo + i;
-                        const uint64_t x = (uint64_t)(aa - tile0) < (uint64_t)tlen
-                                               ? own_q[aa - tile0]
-                                               : read_q(a.qtag + aa, qtag, abort_flag, bad);
-                        stage[i] = tile_pre[aa / kTile] + x;
-                    }
-                }
-            }
-            __syncthreads();
-
+                for (int g = 0; g < kRecGroups; ++g)
+                    if (64 * g < nb) t += __popcll(__ballot(tend[g] <= tau));
+                return min(t, nb - 1);
+            };
+            const int t0 = tile_of(js0), t1 = tile_of(js1);
             int32_t *anc_row = (a.anc_out && nres - 1 < a.max_events) ? a.anc_out + (size_t)(nres - 1) * N : nullptr;
-            if (jb < N) {
-                SlotThreshold th = slot_threshold((uint32_t)jb, Sr, U, NN);
-                if (staged) {
-                    // Each ancestor is the last staged entry <= its slot's tau:
-                    // one before the first entry > tau (span if none).  The
-                    // thread's first slot binary-searches the stage (entry 0, the
-                    // block's first ancestor, is <= tau); later slots count the
-                    // entries <= tau among the kWin after the first slot's
-                    // ancestor, held in registers (one round of LDS loads for all
-                    // slots), and past that window gallop from the previous slot's
-                    // ancestor (whose entry is <= tau) and finish with a binary
-                    // search.
-                    constexpr int kWin = 16;
-                    int lo = 1, hi = span;
-                    {
-                        const uint64_t tau0 = (uint64_t)jb * Sq + th.quo;
-                        while (lo < hi) {
-                            const int mid = (lo + hi) >> 1;
-                            if (stage[mid] > tau0) hi = mid; else lo = mid + 1;
-                        }
+            if (t1 - t0 < kScatterTiles) {
+                // Slot j's ancestor is the last particle a whose exclusive prefix X_a
+                // is <= tau_j, that is whose first slot f_a = min{j: X_a N <= j S + U}
+                // = ceil((X_a N - U) / S) is <= j.  So every particle of those tiles
+                // (this block's own from LDS, the others loaded once) marks slot f_a
+                // with its index (the largest wins), and a running maximum over the
+                // slots fills the rest: no staging of prefix sums and no search per
+                // slot.  f_a is taken in FP64, whose error is below 2^-20 of a slot
+                // for N < 2^31; where the value lies that near a whole number the 128-bit
+                // products decide.
+                const double dS = (double)S, rN = (double)N / dS, cU = (double)U / dS;
+                int before = 0;                      // largest mark of a slot before this block's
+                auto mark = [&](uint64_t X, int id) {
+                    const double d = fma((double)X, rN, -cU), r = __builtin_rint(d);
+                    int64_t f = (int64_t)__builtin_ceil(d);
+                    if (fabs(d - r) < 0x1p-20) {
+                        const int64_t j = (int64_t)r;
+                        const unsigned __int128 lhs = (unsigned __int128)X * NN;
+                        const unsigned __int128 rhs = (unsigned __int128)(uint64_t)max(j, (int64_t)0) * S + U;
+                        f = j >= 0 && lhs <= rhs ? j : j + 1;
                     }
-                    const int pos0 = lo - 1;
-                    uint64_t win[kWin];
+                    const int64_t q = f - js0;
+                    if (q <= 0) before = max(before, id);
+                    else if (q <= js1 - js0) atomicMax(&s_slot[padded((int)q)], id);
+                };
+                __syncthreads();                     // tile_pre
+                const bool own_in = t0 <= (int)blockIdx.x && (int)blockIdx.x <= t1;
+                bool own_done = !own_in;
+                auto mark_own = [&]() {
+                    const uint64_t pre = tile_pre[blockIdx.x];
+                    const int id0 = ((int)blockIdx.x - t0) * kTile + 1;
 #pragma unroll
-                    for (int k = 0; k < kWin; ++k) win[k] = pos0 + 1 + k < span ? stage[pos0 + 1 + k] : ~0ull;
-                    int prev = pos0;
-#pragma unroll 1
-                    for (int p = 0; p < P; ++p) {
-                        const int j = jb + p;
-                        if (j >= N) break;
-                        if (p) slot_threshold_next(th, Sr, NN);
-                        const uint64_t tau = (uint64_t)j * Sq + th.quo;
-                        int c = 0;
-#pragma unroll
-                        for (int k = 0; k < kWin; ++k) c += win[k] <= tau ? 1 : 0;
-                        int idx;
-                        if (c < kWin) {
-                            idx = pos0 + c;
-                        } else {
-                            int l = prev + 1, h = span;
-                            if (l < h) {
-                                if (stage[l] > tau) {
-                                    h = l;
-                                } else {
-                                    int step = 1;
-                                    while (l + step < h && !(stage[l + step] > tau)) {
-                                        l += step;
-                                        step <<= 1;
-                                    }
-                                    h = min(l + step, h);
-                                    ++l;
-                                }
-                            }
-                            while (l < h) {
-                                const int mid = (l + h) >> 1;
-                                if (stage[mid] > tau) h = mid; else l = mid + 1;
-                            }
-                            idx = l - 1;
-                        }
-                        s_anc[threadIdx.x * P + p] = a_lo + idx;
-                        if (anc_row) anc_row[j] = a_lo + idx;
-                        prev = idx;
+                    for (int k = 0; k < P; ++k) {
+                        const int i = threadIdx.x + k * kSmcThreads;
+                        if (i < tlen) mark(pre + own_q[padded(i)], id0 + i);
                     }
-                } else {
-                    int prev = a_lo;
-#pragma unroll 1
-                    for (int p = 0; p < P; ++p) {
-                        const int j = jb + p;
-                        if (j >= N) break;
-                        if (p) slot_threshold_next(th, Sr, NN);
-                        const uint64_t tau = (uint64_t)j * Sq + th.quo;
-                        const int anc = find_ancestor_global(tau, N, nb, kTile, tile_end, tile_pre, a.qtag, qtag, prev,
-                                                             abort_flag, bad);
-                        s_anc[threadIdx.x * P + p] = anc;
-                        if (anc_row) anc_row[j] = anc;
-                        prev = anc;
+                    own_done = true;
+                };
+                for (int t = t0; t <= t1; ++t) {
+                    if (t == (int)blockIdx.x) continue;
+                    const int64_t tb = (int64_t)t * kTile;
+                    const int len = (int)min((int64_t)kTile, N - tb);
+                    const uint64_t pre = tile_pre[t];
+                    uint64_t v[P];
+                    bool cur = false;
+                    for (int tries = 0; !cur && tries < kBatchTries; ++tries) {
+                        // all loads first (clamped in range), then the tags; a word that is
+                        // not yet current makes the wave load the tile again
+                        bool mine = !a.poll_all;
+#pragma unroll
+                        for (int k = 0; k < P; ++k)
+                            v[k] = __hip_atomic_load(a.qtag + tb + min((int)threadIdx.x + k * kSmcThreads, len - 1),
+                                                     __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        if (!own_done) mark_own();   // while those loads run
+#pragma unroll
+                        for (int k = 0; k < P; ++k) mine = mine && (v[k] & ~kQMask) == qtag;
+                        cur = __all(mine);
+                        if (a.poll_all) break;
+                    }
+#pragma unroll
+                    for (int k = 0; k < P; ++k) {
+                        const int i = threadIdx.x + k * kSmcThreads;
+                        if (i < len) {
+                            const uint64_t x = cur ? v[k] & kQMask : read_q(a.qtag + tb + i, qtag, abort_flag, bad);
+                            mark(pre + x, (t - t0) * kTile + 1 + i);
+                        }
                     }
                 }
+                if (!own_done) mark_own();
+                before = wave_max_u32((uint32_t)before);
+                if (lane == 0 && before > 0) atomicMax(&s_slot[0], before);
+                __syncthreads();
+                uint32_t run_max = 0;
+#pragma unroll
+                for (int p = 0; p < P; ++p) {
+                    run_max = max(run_max, (uint32_t)s_slot[padded(threadIdx.x * P + p)]);
+                    anc[p] = (int)run_max;
+                }
+                const uint32_t upto = wave_scan_max_u32(run_max);
+                uint32_t left = (uint32_t)__shfl_up((int)upto, 1, 64);
+                if (lane == 0) left = 0;
+                if (lane == 63) s_cnt[wv] = upto;
+                __syncthreads();
+#pragma unroll
+                for (int w = 0; w < kSmcWaves; ++w)
+                    if (w < wv) left = max(left, s_cnt[w]);
+                const int first = t0 * kTile - 1;
+#pragma unroll
+                for (int p = 0; p < P; ++p) {
+                    anc[p] = first + max(max((int)left, anc[p]), 1);      // 1: only in a run given up
+                    if (anc_row && jb + p < N) anc_row[jb + p] = anc[p];
+                }
+            } else {
+                // Ancestors over many tiles (long runs of particles without weight):
+                // each slot searches for itself.
+                __syncthreads();                     // tile_pre, tile_end
+                SlotThreshold th = slot_threshold((uint32_t)jb, Sr, U, NN, a.inv_n);
+                int prev = t0 * kTile;
+#pragma unroll 1
+                for (int p = 0; p < P; ++p) {
+                    const int j = jb + p;
+                    if (j >= N) break;
+                    if (p) slot_threshold_next(th, Sr, NN);
+                    const uint64_t tau = (uint64_t)j * Sq + th.quo;
+                    prev = find_ancestor_global(tau, N, nb, kTile, tile_end, tile_pre, a.qtag, qtag, prev, abort_flag,
+                                                bad);
+                    s_slot[padded(threadIdx.x * P + p)] = prev;
+                    if (anc_row) anc_row[j] = prev;
+                }
+#pragma unroll
+                for (int p = 0; p < P; ++p) anc[p] = s_slot[padded(threadIdx.x * P + p)];
             }
         }
         if constexpr (!MOVES) {
@@ -954,13 +1020,12 @@ __global__ __launch_bounds__(kSmcThreads) void smc_persistent_kernel(SmcDev a) {
 #pragma unroll
             for (int p = 0; p < P; ++p) {
                 if (!valid[p]) continue;
-                const int anc = s_anc[threadIdx.x * P + p];
-                if (kOwnX && (uint64_t)(anc - tile0) < (uint64_t)tlen) {
-                    st[p][0] = own_x[anc - tile0];      // an ancestor of this block's own tile
+                if (kOwnX && (uint64_t)(anc[p] - tile0) < (uint64_t)tlen) {
+                    st[p][0] = own_x[padded((int)(anc[p] - tile0))];      // an ancestor of this block's own tile
                 } else {
 #pragma unroll
                     for (int f = 0; f < M::NF; ++f) {
-                        const uint64_t v = __hip_atomic_load(a.xtag + (size_t)f * N + anc, __ATOMIC_RELAXED,
+                        const uint64_t v = __hip_atomic_load(a.xtag + (size_t)f * N + anc[p], __ATOMIC_RELAXED,
                                                              __HIP_MEMORY_SCOPE_AGENT);
                         fresh = fresh && (uint32_t)(v >> 32) == xtag;
                         st[p][f] = __uint_as_float((uint32_t)v);
@@ -973,11 +1038,10 @@ __global__ __launch_bounds__(kSmcThreads) void smc_persistent_kernel(SmcDev a) {
 #pragma unroll
                 for (int p = 0; p < P; ++p) {
                     if (!valid[p]) continue;
-                    const int anc = s_anc[threadIdx.x * P + p];
-                    if (kOwnX && (uint64_t)(anc - tile0) < (uint64_t)tlen) continue;
+                        if (kOwnX && (uint64_t)(anc[p] - tile0) < (uint64_t)tlen) continue;
 #pragma unroll
                     for (int f = 0; f < M::NF; ++f)
-                        st[p][f] = read_x(a.xtag + (size_t)f * N + anc, xtag, abort_flag, bad);
+                        st[p][f] = read_x(a.xtag + (size_t)f * N + anc[p], xtag, abort_flag, bad);
                 }
             }
         } else {
@@ -986,10 +1050,9 @@ __global__ __launch_bounds__(kSmcThreads) void smc_persistent_kernel(SmcDev a) {
 #pragma unroll
             for (int p = 0; p < P; ++p) {
                 if (!valid[p]) continue;
-                const int anc = s_anc[threadIdx.x * P + p];
 #pragma unroll
                 for (int f = 0; f < M::NF; ++f)
-                    a.xbuf2[(size_t)f * N + jb + p] = read_x(a.xtag + (size_t)f * N + anc, xtag, abort_flag, bad);
+                    a.xbuf2[(size_t)f * N + jb + p] = read_x(a.xtag + (size_t)f * N + anc[p], xtag, abort_flag, bad);
                 lw[p] = 0.0f;
                 lwc[p] = 0.0f;
             }
@@ -1007,8 +1070,11 @@ __global__ __launch_bounds__(kSmcThreads) void smc_persistent_kernel(SmcDev a) {
                 for (int f = 0; f < M::NF; ++f) st[p][f] = valid[p] ? a.xbuf2[(size_t)f * N + jb + p] : 0.0f;
             }
         }
-        if (__syncthreads_or(bad ? 1 : 0)) { alive = false; break; }   // a tagged read gave up
+        if (bad) L.bad = 1;      // a tagged read gave up: the next wait, or the check after the loop, sees it
     }
+    __syncthreads();
+    if (L.bad) alive = false;
+    flush();
 
     // ---- stop: the run's state into the checkpoint
     const bool stopped = a.t1 < a.T;
@@ -1022,7 +1088,7 @@ __global__ __launch_bounds__(kSmcThreads) void smc_persistent_kernel(SmcDev a) {
             cs[(size_t)M::NF * N + base + p] = lw[p];
             cs[(size_t)(M::NF + 1) * N + base + p] = lwc[p];
         }
-        if (blockIdx.x == 0 && threadIdx.x == 0) {
+        if (blockIdx.x == 0 && book) {
             SmcCkpt *h = (SmcCkpt *)a.ckpt;
             h->t = a.t1;
             h->N = N;
@@ -1046,16 +1112,18 @@ __global__ __launch_bounds__(kSmcThreads) void smc_persistent_kernel(SmcDev a) {
             }
         }
         block_sum2_f64(e1, e2, ldsd);
-        uint32_t rt[4];
-        if (!tagged_barrier<4>(a.rec, a.bar, ++epoch, nb, {hi32(e1), lo32(e1), hi32(e2), lo32(e2)}, rt)) {
+        ++epoch;
+        tagged_post<4>(a.rec, epoch, nb, {hi32(e1), lo32(e1), hi32(e2), lo32(e2)});
+        if (!tagged_wait<4>(a.rec, a.bar, epoch, nb, L)) {
             alive = false;
         } else {
-            double t1 = threadIdx.x < nb ? from32(rt[0], rt[1]) : 0.0;
-            double t2 = threadIdx.x < nb ? from32(rt[2], rt[3]) : 0.0;
+            const int t = threadIdx.x;
+            double t1 = t < nb ? from32(L.w[0][t], L.w[1][t]) : 0.0;
+            double t2 = t < nb ? from32(L.w[2][t], L.w[3][t]) : 0.0;
             block_sum2_f64(t1, t2, ldsd);
             const double inc = (double)Mlast + log_f64(t1) - logN;
             logz += inc;
-            if (a.logz_tr && blockIdx.x == 0 && threadIdx.x == 0) a.logz_tr[a.T - 1] = inc;
+            if (a.logz_tr && blockIdx.x == 0 && book) a.logz_tr[a.T - 1] = inc;
             ess_final = t1 * t1 / t2;
         }
     }
@@ -1071,7 +1139,7 @@ __global__ __launch_bounds__(kSmcThreads) void smc_persistent_kernel(SmcDev a) {
             for (int f = 0; f < M::NF; ++f) a.lat_out[(size_t)f * N + j] = st[p][f];
         }
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
+    if (blockIdx.x == 0 && book) {
         a.scalars[0] = status ? (status == PPL_E_ZERO_WEIGHT ? -INFINITY : NAN) : logz;
         a.scalars[1] = status ? 0.0 : ess_final;
         a.scalars[2] = (double)nres;
@@ -1145,16 +1213,9 @@ static int launch(SmcDev &d, int64_t nb, hipStream_t st) {
     int dev = 0, ncu = 0, occ = 0;
     PPL_HIP(hipGetDevice(&dev));
     PPL_HIP(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
-    // stage as many prefix sums as the per-block LDS limit leaves room for (<= kStage)
-    int max_lds = 0;
-    PPL_HIP(hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev));
-    const int64_t tile = (int64_t)kSmcThreads * P;
-    const int64_t own_x = M::NF == 1 ? tile * (int64_t)sizeof(float) : 0;
-    const int64_t fixed = (int64_t)(2 * nb + tile) * sizeof(uint64_t) + tile * (int64_t)sizeof(int32_t) + own_x +
-                          (int64_t)kYChunk * sizeof(float) + 1024;      // + static LDS of the kernel
-    d.stage_cap = (int)std::max<int64_t>(0, std::min<int64_t>(kStage, (max_lds - fixed) / 8));
-    const size_t lds = (size_t)(2 * nb + d.stage_cap + tile) * sizeof(uint64_t) + (size_t)tile * sizeof(int32_t) +
-                       (size_t)own_x;
+    const int64_t tp = padded_size((int64_t)kSmcThreads * P);
+    const size_t lds = (size_t)(2 * nb + tp) * sizeof(uint64_t) + (size_t)tp * sizeof(int32_t) +
+                       (M::NF == 1 ? (size_t)tp * sizeof(float) : 0);
     PPL_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kern, kSmcThreads, lds));
     if ((int64_t)occ * ncu < nb)
         return fail(PPL_E_UNSUPPORTED, "SMC needs %lld co-resident blocks, device holds %d", (long long)nb, occ * ncu);
@@ -1209,6 +1270,7 @@ int run_smc(const SmcArgs &a, hipStream_t st) {
     int c = 0;
     while (((int64_t)1 << c) < a.N) ++c;
     d.kbits = 62 - c;
+    d.inv_n = ~0ull / (uint64_t)a.N;
     d.scalars = a.out.d_scalars ? a.out.d_scalars : L.scal;
     d.lw_out = (float *)a.out.d_log_weights;
     d.lat_out = (float *)a.out.d_latents;

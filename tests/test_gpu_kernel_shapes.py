@@ -303,3 +303,24 @@ def test_mcmc_shapes(ppl, D, n_lo, n_hi):
             assert abs(summ[m] - (counts[m] / max(1, sum(counts)))) < 1e-12
         if n_lo == 2:
             assert np.allclose(summ[24:], sum(summ[m] * summ[4 + 5 * m:9 + 5 * m] for m in range(4)), rtol=1e-9, atol=1e-9)
+
+
+# --------------------------------------------- resampling of persistent SMC --
+@pytest.mark.parametrize("n,far", [(1, 0.0), (2, 0.0), (511, 4.0), (513, 0.0), (2561, 8.0), (3072, 4.0), (33_000, 12.0),
+                                   ((1 << 17) - 1, 12.0), ((1 << 17) + 1, 6.0), ((1 << 18) + 513, 12.0),
+                                   ((1 << 19) + 4097, 6.0)])
+def test_smc_ancestors_with_far_observations(ppl, orc, n, far):
+    """Every third observation lies `far` away, so an event may leave a handful of
+    particles with weight: a block's ancestors then lie in one tile, in neighbouring
+    tiles or in many, and it finds them by marks or by searches.  Every ancestor
+    follows from the event's own log-weights (the oracle resamples those)."""
+    from forced_check import check_forced
+    from test_gpu_smc import ESS_BAND, run_gpu
+    T, seed = 24, 19
+    y = synthetic.lgssm_data(T=T, seed=43)
+    y[2::3] += np.float32(far)
+    g = run_gpu(ppl, ppl.PPL_MODEL_LGSSM, y, n, seed, ess_frac=0.9, max_events=T, records=True)
+    E = g["n_resample"]
+    f = orc.smc_forced(orc.MODEL_LGSSM, y.astype(np.float64), n, seed, g["resampled"], g["ancestors"][:max(E, 1)],
+                       g["event_lw"][:max(E, 1)], ess_frac=0.9, ess_band=ESS_BAND, want_state=True)
+    print(check_forced(g, f, n, full=True, min_events=0 if n < 3 else 8))
