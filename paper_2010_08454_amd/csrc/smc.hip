@@ -284,15 +284,23 @@ template <int K>
 __device__ double gmm_loglik_upto(const SmcDev &a, int64_t s, const float st[2 * K]) {
     double tot = 0.0;
     float blk = 0.0f;
-    int c = 0;
-    for (int64_t d = 0; d <= s; ++d) {
-        blk += Gmm<K>::step(a, 0.0f, const_cast<float *>(st), a.y[d]);
-        if (++c == 16) {
+    int64_t d = 0;
+    // kSide data side by side, then added in order: one after the other, a
+    // factor's chain of exp, log and adds left the SIMD idle (500 x 20011, K = 4,
+    // one move per event: 4.59 -> 4.19 ms)
+    constexpr int kSide = 4;
+    for (; d + kSide <= s + 1; d += kSide) {
+        float f[kSide];
+#pragma unroll
+        for (int i = 0; i < kSide; ++i) f[i] = Gmm<K>::step(a, 0.0f, const_cast<float *>(st), a.y[d + i]);
+#pragma unroll
+        for (int i = 0; i < kSide; ++i) blk += f[i];
+        if (((d + kSide) & 15) == 0) {
             tot += (double)blk;
             blk = 0.0f;
-            c = 0;
         }
     }
+    for (; d <= s; ++d) blk += Gmm<K>::step(a, 0.0f, const_cast<float *>(st), a.y[d]);
     return tot + (double)blk;
 }
 
