@@ -181,7 +181,8 @@ __device__ __forceinline__ void bt_block_sum_u128x2(u128 &u, u128 &v, uint64_t *
 
 // --------------------------------------------------------------- model ----
 // Mixture with KK <= 8 known components.  State (registers and the staging
-// buffers): log pi_k at [k], mu_k at [KK + k].  Prior draws as in the
+// buffers): 2 log pi_k at [k] (see bt_plain_sum), mu_k at [KK + k]; outputs and
+// moves take half of the former, which is exact.  Prior draws as in the
 // single-instance SMC.
 template <int KK>
 __device__ __forceinline__ void bt_init(uint32_t j, uint32_t c3, Key key, float mu_sd, float st[2 * KK]) {
@@ -198,7 +199,7 @@ __device__ __forceinline__ void bt_init(uint32_t j, uint32_t c3, Key key, float 
     normals4(philox(j, 3, 0, c3, key), z + 4);
 #pragma unroll
     for (int k = 0; k < KK; ++k) {
-        st[k] = logf(E[k] / tot);
+        st[k] = 2.0f * logf(E[k] / tot);
         st[KK + k] = mu_sd * z[k];
     }
 }
@@ -213,44 +214,58 @@ __device__ __forceinline__ void bt_init(uint32_t j, uint32_t c3, Key key, float 
 // more than a few bits to underflow).  A datum far from every mean gives a
 // smaller sum, and the factor is then the sum shifted by its largest term.
 // Which form a particle takes depends on its own terms only.
+//
+// This is bound by VALU issue, so its instructions are counted.  st holds
+// 2 log pi_k: 2 t_k = fma(-r, r, 2 log pi_k) and exp(t_k) = 2^(2 t_k log2(e) / 2)
+// are t_k and exp(t_k) to the bit (scaling by two is exact) without a multiply by
+// -1/2 per component.  A plain sum above kBtTiny is a normal number of at most
+// about KK, so its logarithm needs no handling of subnormal and infinite
+// arguments (seven of fourteen instructions).  Measured with the compensated sums
+// of full waves free of selects: 64 instances x 2^16 particles, D = 10^2 .. 10^4.5,
+// eight particles per lane: 80.3 -> 72.1 ms; 256 x 2^14, D = 10^2 .. 10^3: 18.7 ->
+// 18.5 ms (bound by events).  Recomputing the terms in the shifted form instead of
+// keeping them was slower where far data are common (18.4 -> 21.8 ms).
 constexpr float kBtTiny = 1e-30f;
+constexpr float kBtHalfLog2e = 0x1.715476p-1f;    // log2(e) / 2
 
-template <int KK>
-__device__ __forceinline__ void bt_terms(const float *st, float inv_sd, float ys, float (&t)[KK]) {
-#pragma unroll
-    for (int k = 0; k < KK; ++k) {
-        const float r = (ys - st[KK + k]) * inv_sd;
-        t[k] = fmaf(-0.5f * r, r, st[k]);
-    }
+// log x for normal positive x: log2(x) times ln 2 in two parts (a NaN stays NaN).
+__device__ __forceinline__ float bt_log_normal(float x) {
+    const float hi = 0x1.62e42ep-1f, lo = 0x1.efa39ep-25f;
+    const float l = __builtin_amdgcn_logf(x);
+    return fmaf(l, hi, fmaf(l, lo, fmaf(l, hi, -(l * hi))));
 }
 
 template <int KK>
 __device__ __forceinline__ float bt_plain_sum(const float *st, float inv_sd, float ys) {
-    float t[KK];
-    bt_terms<KK>(st, inv_sd, ys, t);
     float s = 0.0f;
 #pragma unroll
-    for (int k = 0; k < KK; ++k) s += __expf(t[k]);
+    for (int k = 0; k < KK; ++k) {
+        const float r = (ys - st[KK + k]) * inv_sd;
+        const float e = __builtin_amdgcn_exp2f(fmaf(-r, r, st[k]) * kBtHalfLog2e);
+        s = k ? s + e : e;
+    }
     return s;
 }
 
 template <int KK>
 __device__ __forceinline__ float bt_shifted(const float *st, float inv_sd, float lconst, float ys) {
-    float t[KK];
-    bt_terms<KK>(st, inv_sd, ys, t);
-    float mx = t[0];
+    float t[KK], mx = -INFINITY;
 #pragma unroll
-    for (int k = 1; k < KK; ++k) mx = fmaxf(mx, t[k]);
+    for (int k = 0; k < KK; ++k) {
+        const float r = (ys - st[KK + k]) * inv_sd;
+        t[k] = fmaf(-r, r, st[k]);
+        mx = k ? fmaxf(mx, t[k]) : t[k];
+    }
     float s = 0.0f;
 #pragma unroll
-    for (int k = 0; k < KK; ++k) s += __expf(t[k] - mx);
-    return lconst + mx + __logf(s);
+    for (int k = 0; k < KK; ++k) s += __builtin_amdgcn_exp2f((t[k] - mx) * kBtHalfLog2e);
+    return lconst + 0.5f * mx + bt_log_normal(s);       // s in [1, KK] or NaN
 }
 
 template <int KK>
 __device__ __forceinline__ float bt_factor(const float *st, float inv_sd, float lconst, float ys) {
     const float s = bt_plain_sum<KK>(st, inv_sd, ys);
-    return s > kBtTiny ? lconst + __logf(s) : bt_shifted<KK>(st, inv_sd, lconst, ys);
+    return s > kBtTiny ? lconst + bt_log_normal(s) : bt_shifted<KK>(st, inv_sd, lconst, ys);
 }
 
 // The factors of a thread's P particles for one datum: the plain sums first
@@ -260,19 +275,24 @@ __device__ __forceinline__ float bt_factor(const float *st, float inv_sd, float 
 template <int P, int KK>
 __device__ __forceinline__ void bt_factors(const float (&st)[P][2 * KK], float inv_sd, float lconst, float ys,
                                            float (&f)[P]) {
-    float s[P];
-    bool small = false;
+    float s[P], least = INFINITY;
 #pragma unroll
     for (int p = 0; p < P; ++p) {
         s[p] = bt_plain_sum<KK>(st[p], inv_sd, ys);
-        small = small || !(s[p] > kBtTiny);
+        least = fminf(least, s[p]);
     }
 #pragma unroll
-    for (int p = 0; p < P; ++p) f[p] = lconst + __logf(s[p]);
-    if (__ballot(small)) {
+    for (int p = 0; p < P; ++p) f[p] = lconst + bt_log_normal(s[p]);
+    // A NaN sum gives NaN in either form.  The branches are uniform and the lanes
+    // select: no lane is masked off where a register may have to be spilled.
+    if (__ballot(!(least > kBtTiny))) {
 #pragma unroll
-        for (int p = 0; p < P; ++p)
-            if (!(s[p] > kBtTiny)) f[p] = bt_shifted<KK>(st[p], inv_sd, lconst, ys);
+        for (int p = 0; p < P; ++p) {
+            if (__ballot(!(s[p] > kBtTiny))) {
+                const float g = bt_shifted<KK>(st[p], inv_sd, lconst, ys);
+                f[p] = s[p] > kBtTiny ? f[p] : g;
+            }
+        }
     }
 }
 
@@ -282,20 +302,42 @@ __device__ __forceinline__ void bt_factors(const float (&st)[P][2 * KK], float i
 // steps whose target is the posterior given y_0..y_s, with the mixture factor
 // of this engine (FP32, summed in FP32 within blocks of 16 data and in FP64
 // across them).  State: log pi_k at [k], mu_k at [KK + k].
+// The factors of four data are evaluated side by side, then added in order: one
+// after the other, a factor's chain of exp, log and adds left the SIMD idle
+// (16 instances x 20011 particles, one move per event: 50.3 -> 37.4 ms).
 template <int KK>
-__device__ double bt_loglik_upto(const float *st, const float *__restrict__ y, int64_t s, float inv_sd,
+__device__ double bt_loglik_upto(const float *st1, const float *__restrict__ y, int64_t s, float inv_sd,
                                  float lconst) {
+    float st[1][2 * KK];
+#pragma unroll
+    for (int f = 0; f < 2 * KK; ++f) st[0][f] = f < KK ? 2.0f * st1[f] : st1[f];
     double tot = 0.0;
     float blk = 0.0f;
-    int c = 0;
-    for (int64_t d = 0; d <= s; ++d) {
-        blk += bt_factor<KK>(st, inv_sd, lconst, y[d]);
-        if (++c == 16) {
+    int64_t d = 0;
+    for (; d + 4 <= s + 1; d += 4) {
+        float sum[4], f[4], least = INFINITY;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            sum[i] = bt_plain_sum<KK>(st[0], inv_sd, y[d + i]);
+            least = fminf(least, sum[i]);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) f[i] = lconst + bt_log_normal(sum[i]);
+        if (__ballot(!(least > kBtTiny))) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float g = bt_shifted<KK>(st[0], inv_sd, lconst, y[d + i]);
+                f[i] = sum[i] > kBtTiny ? f[i] : g;
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) blk += f[i];
+        if (((d + 4) & 15) == 0) {
             tot += (double)blk;
             blk = 0.0f;
-            c = 0;
         }
     }
+    for (; d <= s; ++d) blk += bt_factor<KK>(st[0], inv_sd, lconst, y[d]);
     return tot + (double)blk;
 }
 
@@ -325,7 +367,7 @@ __device__ void bt_move(float *g, size_t stride, int64_t s, uint32_t j, BtMove m
     float st[2 * KK];
 #pragma unroll
     for (int k = 0; k < KK; ++k) {
-        st[k] = g[k * stride];
+        st[k] = 0.5f * g[k * stride];
         st[KK + k] = g[(KK + k) * stride];
     }
     double ll = bt_loglik_upto<KK>(st, mv.y, s, mv.inv_sd, mv.lconst);
@@ -367,44 +409,52 @@ __device__ void bt_move(float *g, size_t stride, int64_t s, uint32_t j, BtMove m
     }
 #pragma unroll
     for (int k = 0; k < KK; ++k) {
-        g[k * stride] = st[k];
+        g[k * stride] = 2.0f * st[k];
         g[(KK + k) * stride] = st[KK + k];
     }
 }
 
 // One speculative block: advance every particle's log-weight over the tb
 // data in ybuf and record, per factor, the wave's {max, s1, s2} of the
-// log-weights in wpart (a NaN log-weight poisons s1).
+// log-weights in wpart (a NaN log-weight makes s1 NaN).  A wave with slots
+// beyond the last particle puts those back to weight zero after each factor;
+// the others need no select per particle.
 template <int P, int KK>
 __device__ __forceinline__ void bt_block_factors(const float (&st)[P][2 * KK], const bool (&valid)[P], float (&lw)[P],
-                                                 float (&lwc)[P],
-                                                 const float *ybuf, int tb, float inv_sd, float lconst,
-                                                 float (*wpart)[kBtWaves][3], int wave, int lane) {
+                                                 float (&lwc)[P], const float *ybuf, int tb, float inv_sd,
+                                                 float lconst, float (*wpart)[kBtWaves][3], int wave, int lane) {
+    const bool full = __all(valid[P - 1]);       // a thread's slots are consecutive
     for (int t = 0; t < tb; ++t) {
         const float ys = ybuf[t];
         float ml = -INFINITY;
-        int nan_seen = 0;
         float f[P];
         bt_factors<P, KK>(st, inv_sd, lconst, ys, f);
 #pragma unroll
-        for (int p = 0; p < P; ++p) {
-            if (valid[p]) kahan_add(lw[p], lwc[p], f[p]);
-            ml = fmaxf(ml, lw[p]);
-            nan_seen |= isnan(lw[p]) ? 1 : 0;
+        for (int p = 0; p < P; ++p) kahan_add(lw[p], lwc[p], f[p]);
+        if (!full) {
+#pragma unroll
+            for (int p = 0; p < P; ++p) {
+                lw[p] = valid[p] ? lw[p] : -INFINITY;
+                lwc[p] = valid[p] ? lwc[p] : 0.0f;
+            }
         }
+#pragma unroll
+        for (int p = 0; p < P; ++p) ml = fmaxf(ml, lw[p]);
         const float mw = wave_max_dpp(ml);
         float s1 = 0.0f, s2 = 0.0f;
-        if (mw > -INFINITY) {
+        if (mw > -INFINITY) {                    // a NaN log-weight gives e = NaN
 #pragma unroll
             for (int p = 0; p < P; ++p) {
                 const float e = __expf(lw[p] - mw);
                 s1 += e;
                 s2 = fmaf(e, e, s2);
             }
+        } else {
+#pragma unroll
+            for (int p = 0; p < P; ++p) s1 = isnan(lw[p]) ? NAN : s1;
         }
         s1 = wave_sum_dpp(s1);
         s2 = wave_sum_dpp(s2);
-        if (__ballot(nan_seen != 0)) s1 = NAN;
         if (lane == 0) {
             wpart[t][wave][0] = mw;
             wpart[t][wave][1] = s1;
@@ -893,7 +943,7 @@ __device__ __forceinline__ void bt_instance(const BtDev &a, BtCtx &cx, int i) {
         if (a.lw_out) a.lw_out[poff + j] = lw[p];
         if (a.lat_out) {
 #pragma unroll
-            for (int f = 0; f < 2 * KK; ++f) a.lat_out[(size_t)kBtNF * poff + (size_t)f * N + j] = st[p][f];
+            for (int f = 0; f < 2 * KK; ++f) a.lat_out[(size_t)kBtNF * poff + (size_t)f * N + j] = f < KK ? 0.5f * st[p][f] : st[p][f];
         }
     }
     if (a.counters && wg == 0 && threadIdx.x == 0) {

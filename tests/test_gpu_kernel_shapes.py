@@ -324,3 +324,33 @@ def test_smc_ancestors_with_far_observations(ppl, orc, n, far):
     f = orc.smc_forced(orc.MODEL_LGSSM, y.astype(np.float64), n, seed, g["resampled"], g["ancestors"][:max(E, 1)],
                        g["event_lw"][:max(E, 1)], ess_frac=0.9, ess_band=ESS_BAND, want_state=True)
     print(check_forced(g, f, n, full=True, min_events=0 if n < 3 else 8))
+
+
+# --------------------------------------------------------- batched mixtures --
+@pytest.mark.parametrize("moves", [0, 1])
+@pytest.mark.parametrize("K", range(1, 9))
+def test_batched_every_instantiation(ppl, K, moves):
+    """Every component count at 1, 2, 4 and 8 particles per lane and blocks of 1
+    and 64 factors, with slots beyond the last particle (700, 4097) and without
+    (4096), a far observation (the shifted form of the factor) and a length that
+    leaves a remainder of the moves' side by side data.  The particles and the
+    normaliser are the same bits for every launch shape, and log Z-hat is the sum
+    of its trace (D additions of values up to |log Z-hat| in another order)."""
+    from test_gpu_batched import run_batch
+    rng = np.random.default_rng(1000 + K)
+    batch = []
+    for D, N in ((67, 700), (50, 4097), (90, 4096)):
+        y = (rng.normal(size=K) * 10.0)[rng.integers(0, K, D)] + rng.normal(size=D)
+        y[D // 2] += 80.0
+        batch.append((K, y.astype(np.float32), N))
+    ref = None
+    for tune in ((4, 0, 64, 0), (1, 0, 64, 0), (2, 0, 64, 0), (8, 0, 64, 0), (8, 0, 1, 0)):
+        g = run_batch(ppl, batch, 5, tune=tune, max_events=90, move_steps=moves)
+        for i, gi in enumerate(g):
+            D = batch[i][1].size
+            assert gi["status"] == 0
+            assert abs(np.nansum(gi["logz_trace"]) - gi["log_z"]) <= D * 2.0 ** -52 * (abs(gi["log_z"]) + 1.0)
+            if ref is not None:
+                for key in ("log_z", "n_resample", "lw", "state", "ancestors"):
+                    np.testing.assert_array_equal(np.asarray(gi[key]), np.asarray(ref[i][key]))
+        ref = g if ref is None else ref
