@@ -123,14 +123,18 @@ def _check(rc):
     return rc
 
 
+# Pointers and streams go to the library as plain integers: every entry point has
+# its argument types declared and every struct field is a c_void_p, which take
+# them, and a small call is bound by the time spent here (polynomial importance
+# sampling of 10^4 particles over 10 points: 10.9 -> 9.3 us a call).
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream(stream):
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+    if stream is None:                      # torch.cuda.current_stream() without its Stream object
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return stream.cuda_stream
 
 
 def make_data(x, y, n_data=None, dim=0, hyper=None, dtype=None):
