@@ -778,7 +778,7 @@ static int forward_backward(int model, int K, const MlpView &w, const TrainBufs 
                             hipStream_t st) {
     const char *e = getenv("PPL_TRAIN_UNFUSED");
     if (!(e && e[0] == '1')) return launch_fused_pass(model, K, w, b, adv, st);
-    if (int rc = launch_forward(w, b, true, st)) return rc;
+    if (int rc = launch_forward(w, b, st)) return rc;
     if (int rc = launch_head_backward(model, K, w, b, st)) return rc;
     return launch_advance(adv, st);
 }

@@ -479,17 +479,6 @@ __device__ __forceinline__ void bt_block_redo(const float (&st)[P][2 * KK], cons
 }
 
 // --------------------------------------------------------- LDS helpers ----
-__device__ __forceinline__ float bt_block_max(float v, float *lds) {
-    v = wave_max_dpp(v);
-    if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = v;
-    __syncthreads();
-    float m = lds[0];
-#pragma unroll
-    for (int w = 1; w < kBtWaves; ++w) m = fmaxf(m, lds[w]);
-    __syncthreads();
-    return m;
-}
-
 // Sum over the workgroup (waves in a fixed order; lds: kBtWaves doubles).
 __device__ __forceinline__ double bt_block_sum_f64(double v, double *lds) {
     v = wave_sum_dpp(v);

@@ -299,11 +299,6 @@ __device__ __forceinline__ double wave_max_dpp(double v) {
     const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), 63);
     return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
 }
-__device__ __forceinline__ int wave_or(int v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v |= __shfl_xor(v, o, 64);
-    return v;
-}
 
 // ------------------------------------------- weighted-sum partial records --
 // A partial over a set of particles: {m = max lw, s1 = sum e, s2 = sum e^2,

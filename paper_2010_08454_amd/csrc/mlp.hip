@@ -43,7 +43,6 @@ int mlp_gemm(const uint16_t *A, const uint16_t *B, int M, int N, int R, int lda,
     switch (epi) {
 #define PPL_EPI(E) case (E): launch_gemm<(E)>(A, B, M, N, R, lda, ldb, bias, mask, out_row, out_col, out_f32, R, 1, st); break;
         PPL_EPI(kEpiBias | kEpiRelu | kEpiOutRow | kEpiOutCol)
-        PPL_EPI(kEpiBias | kEpiRelu | kEpiOutRow)
         PPL_EPI(kEpiBias | kEpiOutF32Col)
         PPL_EPI(kEpiMaskRow | kEpiOutRow | kEpiOutCol)
         PPL_EPI(kEpiMaskRow | kEpiOutCol)

@@ -75,7 +75,7 @@ struct AdvanceJob {
 AdvanceJob advance_job(int64_t *step, const TrainBufs &b, const AdamSpec &ad, double *loss_trace);
 
 // Forward pass of a batch whose summaries are already in bufs.x_row/x_col.
-int launch_forward(const MlpView &w, const TrainBufs &b, bool keep_cols, hipStream_t st);
+int launch_forward(const MlpView &w, const TrainBufs &b, hipStream_t st);
 // Loss head and backward pass (gradients left in the split partials and bgrad).
 int launch_head_backward(int model, int K, const MlpView &w, const TrainBufs &b, hipStream_t st);
 // The same in fewer launches: forward, head and input gradients fused per 32

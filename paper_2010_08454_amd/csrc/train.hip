@@ -516,8 +516,8 @@ TrainBufs train_bufs(void *ws, int B) {
     return t;
 }
 
-int launch_forward(const MlpView &w, const TrainBufs &b, bool keep_cols, hipStream_t st) {
-    const int epi = kEpiBias | kEpiRelu | kEpiOutRow | (keep_cols ? kEpiOutCol : 0);
+int launch_forward(const MlpView &w, const TrainBufs &b, hipStream_t st) {
+    const int epi = kEpiBias | kEpiRelu | kEpiOutRow | kEpiOutCol;
     if (int rc = mlp_gemm(b.x_row, w.wt + MlpParams::bf16_w_off(0), b.B, kMlpHid, kMlpIn, kMlpIn, kMlpIn, epi,
                           w.master + MlpParams::b_off(0), nullptr, b.h1_row, b.h1_col, nullptr, st))
         return rc;
