@@ -354,3 +354,31 @@ def test_batched_every_instantiation(ppl, K, moves):
                 for key in ("log_z", "n_resample", "lw", "state", "ancestors"):
                     np.testing.assert_array_equal(np.asarray(gi[key]), np.asarray(ref[i][key]))
         ref = g if ref is None else ref
+
+
+# ------------------------------------------------------ standalone resampling --
+@pytest.mark.parametrize("n", [1, 2, 63, 1023, 1025, 2048, 2049, 8192, 8193, 20_000, 2048 * 256, 2048 * 256 + 1])
+@pytest.mark.parametrize("kind", ["even", "one", "ends", "zero"])
+def test_resample_launch_shapes(ppl, orc, n, kind):
+    """Entry counts on both sides of the rules for own maxima and local tile
+    prefixes.  The weights are 0 or 1 (log-weights 0 or -inf), which quantise
+    exactly, so every ancestor is the oracle's."""
+    import torch
+    lw = np.full(n, -np.inf, dtype=np.float32)
+    if kind == "even":
+        lw[::2] = 0.0
+    elif kind == "one":
+        lw[n // 3] = 0.0
+    elif kind == "ends":
+        lw[0] = lw[-1] = 0.0
+    state = np.arange(5 * n, dtype=np.float32).reshape(5, n)
+    anc = torch.full((n,), -7, dtype=torch.int32, device="cuda")
+    out = ppl.ppl_resample_gather(torch.from_numpy(lw).cuda(), torch.from_numpy(state).cuda(), seed=6, step=2, inst=1,
+                                  anc=anc).cpu().numpy()
+    got = anc.cpu().numpy()
+    if kind == "zero":
+        assert np.all(got == -1) and np.all(np.isnan(out))
+        return
+    ref, _ = orc.resample(lw.astype(np.float64), seed=6, step=2, inst=1, band=0.0)
+    np.testing.assert_array_equal(got, ref)
+    np.testing.assert_array_equal(out, state[:, ref])
