@@ -23,7 +23,7 @@
 // records travel, and a particle marks its slots instead of every slot searching
 // (8 slots per thread: 6.6 us of search and 1.3 us of staging per event).
 // Measured against merging by one wave, serial polls and a search per slot:
-// 1000 x 2^20 30.1 -> 21.8 ms, 300 x 1000 3.30 -> 2.03 ms, 300 x 100003 4.55 ->
+// 1000 x 2^20 30.1 -> 21.4 ms, 300 x 1000 3.30 -> 2.03 ms, 300 x 100003 4.55 ->
 // 3.34 ms, mixture 300 x 20011 with K = 4 1.35 -> 1.26 ms; the noise drawn
 // while records travel is 3.2 ms of the first.
 // Per factor s:
@@ -689,10 +689,12 @@ __global__ __launch_bounds__(kSmcThreads) void smc_persistent_kernel(SmcDev a) {
     };
     if (threadIdx.x == 0) L.bad = 0;
     __syncthreads();
-    float zn[M::kNoise ? P : 1][2];          // the factor pair's noise
+    // the factor pair's noise: two arrays, so that the choice between them is one of
+    // values (an array's element at s mod 2 is an address and lives in scratch memory)
+    float zn0[P], zn1[P];
     if constexpr (M::kNoise) {
 #pragma unroll
-        for (int p = 0; p < P; ++p) M::noise(a, a.t0 & ~(int64_t)1, (uint32_t)(base + p), zn[p][0], zn[p][1]);
+        for (int p = 0; p < P; ++p) M::noise(a, a.t0 & ~(int64_t)1, (uint32_t)(base + p), zn0[p], zn1[p]);
     }
     for (int64_t s = a.t0; status == 0 && s < a.t1; ++s) {
         if (s == a.t0 || (s % kYChunk) == 0) {     // stage the chunk of observations holding factor s
@@ -709,7 +711,9 @@ __global__ __launch_bounds__(kSmcThreads) void smc_persistent_kernel(SmcDev a) {
         asm volatile("" : "+v"(jb));
 #pragma unroll
         for (int p = 0; p < P; ++p) {
-            const float f = M::step(a, M::kNoise ? ((s & 1) ? zn[M::kNoise ? p : 0][1] : zn[M::kNoise ? p : 0][0]) : 0.0f, st[p], ys);
+            float z = 0.0f;
+            if constexpr (M::kNoise) z = (s & 1) ? zn1[p] : zn0[p];
+            const float f = M::step(a, z, st[p], ys);
             if (valid[p]) kahan_add(lw[p], lwc[p], f);
         }
         // block partial for the ESS trigger
@@ -756,7 +760,7 @@ __global__ __launch_bounds__(kSmcThreads) void smc_persistent_kernel(SmcDev a) {
         if constexpr (M::kNoise) {
             if ((s & 1) && s + 1 < a.t1) {
 #pragma unroll
-                for (int p = 0; p < P; ++p) M::noise(a, s + 1, (uint32_t)(jb + p), zn[p][0], zn[p][1]);
+                for (int p = 0; p < P; ++p) M::noise(a, s + 1, (uint32_t)(jb + p), zn0[p], zn1[p]);
             }
         }
         if (!tagged_wait<5>(a.rec, a.bar, epoch, nb, L)) {
