@@ -69,6 +69,19 @@ __device__ __forceinline__ double mc_loglik(const double pc[5], const double *__
     return -0.5 * acc;
 }
 
+// log k for the trace-size ratio, k = n + 1 in [2, 6] (each literal the nearest
+// double).  A chain of selects between literals; selects between the elements of a
+// table are folded back into a load at a run-time index, which is an LDS table or
+// scratch memory inside the iteration.
+__device__ __forceinline__ double log_size(int k) {
+    double r = 0x1.62e42fefa39efp-1;
+    r = k == 3 ? 0x1.193ea7aad030bp+0 : r;
+    r = k == 4 ? 0x1.62e42fefa39efp+0 : r;
+    r = k == 5 ? 0x1.9c041f7ed8d33p+0 : r;
+    r = k == 6 ? 0x1.cab0bfa2a2002p+0 : r;
+    return r;
+}
+
 __global__ __launch_bounds__(kMcThreads) void mcmc_poly_kernel(
     const double *__restrict__ X, const double *__restrict__ Y, int D, int64_t C, int64_t T, int64_t burn,
     Key key, double sd, int n_lo, int n_hi, double *__restrict__ state_out, int64_t *__restrict__ acc_out,
@@ -86,18 +99,6 @@ __global__ __launch_bounds__(kMcThreads) void mcmc_poly_kernel(
 #pragma unroll
     for (int k = 0; k < kMcNF; ++k) sums[k] = 0.0;
     const uint32_t range = (uint32_t)(n_hi - n_lo + 1);
-    // log(n + 1) for the trace-size ratio, n <= 5: the same values log() gives
-    // per iteration, computed once
-    double lsz[7];
-#pragma unroll
-    for (int k = 1; k <= 6; ++k) lsz[k] = log((double)k);
-    lsz[0] = 0.0;
-    auto log_size = [&](int k) {
-        double r = lsz[1];
-#pragma unroll
-        for (int q = 2; q <= 6; ++q) r = k == q ? lsz[q] : r;
-        return r;
-    };
 
     for (int64_t t = 0; t < T; ++t) {
         const uint4 w = philox((uint32_t)c, (uint32_t)(3 * t), 0, kTagMcmc, key);
@@ -186,9 +187,10 @@ __global__ __launch_bounds__(kMcThreads) void mcmc_poly_kernel(
 // of the iteration's three Philox blocks and its Box-Muller pair, takes every
 // fourth point, from LDS, and keeps the sums of degree 2 + b.
 // Bound: the latency of one iteration, with two waves per SIMD its issue.  us a call
-// against a lane per chain: 1000 chains x 1000 iterations x 200 points 2002 and
-// 4424, 10007 x 300 x 100 458 and 925, 2^15 x 300 x 200 948 and 1350; 20000 x 300
-// x 30 673 and about 610.
+// against a lane per chain: 1000 chains x 1000 iterations x 200 points 1889 and
+// 4424, 10007 x 300 x 100 427 and 925, 2^15 x 300 x 200 920 and 1350 (1999, 460 and
+// 947 with the trace-size logarithms in scratch memory; so too 20000 x 300 x 30
+// 673 and about 610).
 constexpr int kMcQuadChains = 32768;
 constexpr int kMcQuadPoints = 2048;         // most points in LDS (32 KB)
 
@@ -243,15 +245,6 @@ __global__ __launch_bounds__(kMcThreads) void mcmc_poly_quad_kernel(
 #pragma unroll
     for (int k = 0; k < kSums; ++k) sums[k] = 0.0;
     const uint32_t range = (uint32_t)(n_hi - n_lo + 1);
-    double lsz[7];
-#pragma unroll
-    for (int k = 1; k <= 6; ++k) lsz[k] = log((double)k);
-    auto log_size = [&](int k) {
-        double r = lsz[1];
-#pragma unroll
-        for (int q = 2; q <= 6; ++q) r = k == q ? lsz[q] : r;
-        return r;
-    };
     for (int64_t t = 0; t < T; ++t) {
         const uint4 w = philox((uint32_t)c, (uint32_t)(3 * t) + (uint32_t)min(b, 2), 0, kTagMcmc, key);
         const int site = uniform_discrete(word0(w.x), 0, (uint32_t)(n + 1));

@@ -52,3 +52,14 @@ def test_state_space_filter_keeps_its_state_in_registers(kernels):
     mine = {n: k for n, k in kernels.items() if "smc_persistent_kernelINS_5LgssmE" in n}
     assert len(mine) == 8
     assert {n: k[".private_segment_fixed_size"] for n, k in mine.items()} == {n: 0 for n in mine}
+
+
+def test_chains_keep_their_tables_in_registers(kernels):
+    """Neither scratch memory nor an LDS table inside a Metropolis-Hastings
+    iteration: the static LDS is the reduction's alone (30 sums of four waves, 8
+    of four lanes for every row of 16)."""
+    lds = {"mcmc_poly_kernelE": 30 * 4 * 8, "mcmc_poly_quad_kernelE": 16 * 4 * 8 * 8}
+    for part, size in lds.items():
+        k, = [k for n, k in kernels.items() if part in n]
+        assert k[".private_segment_fixed_size"] == 0
+        assert k[".group_segment_fixed_size"] == size
