@@ -359,7 +359,10 @@ typedef struct ppl_mcmc_result {
  * z_1.. for fresh ones).  Chain c starts from the prior draw of importance
  * sampling's execution c.  FP64 throughout.  n_chains in [1, 2^31),
  * n_iters >= 0, 0 <= burn_in <= n_iters.  Workspace: PPL_ALGO_MCMC bytes
- * for n_chains (ppl_workspace_size with n_particles = n_chains). */
+ * for n_chains (ppl_workspace_size with n_particles = n_chains); one of at
+ * least 256 + 240 ceil(n_chains / 256) bytes, rounded up to 256, is accepted
+ * too: small calls then run on fewer workgroups, their FP64 likelihood sums
+ * taken in another order. */
 int ppl_mcmc(int model, const ppl_data *data, int64_t n_chains, int64_t n_iters, int64_t burn_in, uint64_t seed,
              void *d_ws, size_t ws_bytes, void *stream, ppl_mcmc_result *out);
 

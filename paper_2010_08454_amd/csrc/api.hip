@@ -441,7 +441,7 @@ int ppl_mcmc(int model, const ppl_data *data, int64_t n_chains, int64_t n_iters,
     if (int rc = check_model_data(model, data, a.hyper)) return rc;
     if ((out->d_n_trace || out->d_log_alpha) && (double)n_iters * (double)n_chains > 4e12)
         return fail(PPL_E_ARG, "trace of %lld x %lld entries is too large", (long long)n_iters, (long long)n_chains);
-    if (int rc = check_ws(ws, ws_bytes, mcmc_ws_bytes(n_chains))) return rc;
+    if (int rc = check_ws(ws, ws_bytes, mcmc_ws_min_bytes(n_chains))) return rc;
     if (int rc = check_device()) return rc;
     a.x = (const double *)data->x;
     a.y = (const double *)data->y;
@@ -457,6 +457,7 @@ int ppl_mcmc(int model, const ppl_data *data, int64_t n_chains, int64_t n_iters,
     a.summaries = out->d_summaries;
     a.scalars = out->d_scalars ? out->d_scalars : (double *)ws;
     a.ws = ws;
+    a.ws_bytes = ws_bytes;
     hipStream_t st = (hipStream_t)stream;
     if (int rc = run_mcmc_poly(a, st)) return rc;
     if (out->sync_host) {

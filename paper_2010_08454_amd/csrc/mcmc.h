@@ -19,9 +19,11 @@ struct McmcArgs {
     double *summaries;       // [29] or null
     double *scalars;         // [4] device
     void *ws;
+    size_t ws_bytes;         // mcmc_ws_min_bytes or more; mcmc_ws_bytes let small calls use more workgroups
 };
 
 size_t mcmc_ws_bytes(int64_t chains);
+size_t mcmc_ws_min_bytes(int64_t chains);
 int run_mcmc_poly(const McmcArgs &a, hipStream_t st);
 
 }  // namespace ppl

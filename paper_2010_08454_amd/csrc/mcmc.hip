@@ -359,16 +359,23 @@ __global__ __launch_bounds__(1024) void mcmc_finalize_kernel(const double *__res
     scalars[3] = 0.0;
 }
 
+static size_t mcmc_bytes(int64_t records) { return 256 + align_up((size_t)records * kMcNF * sizeof(double), 256); }
+
+size_t mcmc_ws_min_bytes(int64_t chains) { return mcmc_bytes((chains + kMcThreads - 1) / kMcThreads); }
+
 // Room for the quad kernel's records at every chain count it may take, so that
 // the size never falls as the chains grow.
 size_t mcmc_ws_bytes(int64_t chains) {
-    const int64_t blocks = (chains + kMcThreads - 1) / kMcThreads;
     const int64_t quads = (std::min<int64_t>(chains, kMcQuadChains) + kMcThreads / 4 - 1) / (kMcThreads / 4);
-    return 256 + align_up((size_t)std::max(blocks, quads) * kMcNF * sizeof(double), 256);
+    return std::max(mcmc_ws_min_bytes(chains), mcmc_bytes(quads));
 }
 
+// A workspace too small for the quad kernel's records takes a lane per chain (four
+// times fewer records), which is also faster there than quads in workgroups of 1024
+// threads with as few records (1000 chains x 1000 iterations x 200 points: 6.0 ms).
 int run_mcmc_poly(const McmcArgs &a, hipStream_t st) {
-    const bool quad = a.C <= (a.D < 64 ? kMcQuadChains / 2 : kMcQuadChains) && a.D <= kMcQuadPoints;
+    const bool quad = a.C <= (a.D < 64 ? kMcQuadChains / 2 : kMcQuadChains) && a.D <= kMcQuadPoints &&
+                      a.ws_bytes >= mcmc_ws_bytes(a.C);
     const int64_t per = quad ? kMcThreads / 4 : kMcThreads;
     const int64_t blocks = (a.C + per - 1) / per;
     if (int rc = check_grid("mcmc_poly_kernel", blocks, kMcThreads)) return rc;

@@ -101,3 +101,39 @@ def test_mcmc_rejects_bad_arguments(ppl):
     with pytest.raises(ppl.PplError) as e:
         ppl.ppl_mcmc(ppl.PPL_MODEL_BLR, data, 10, 10, 1, ws=ppl.workspace(1 << 20))
     assert e.value.code == ppl.PPL_E_MODEL
+
+
+@pytest.mark.parametrize("C,D", [(65, 5), (1000, 20), (4097, 100), (16384, 33), (32768, 100)])
+def test_mcmc_least_workspace(ppl, C, D):
+    """A workspace of 256 + 240 ceil(C / 256) bytes, rounded up to 256, takes every
+    call, with the same chains; one byte less is refused.  A likelihood sum in
+    another order (D terms of one sign) moves log alpha by at most D 2^-52 of
+    the log-likelihoods' size, a summary (sums of C (T - burn) terms) by 1e-10."""
+    import torch
+    x, y = synthetic.poly_data(D=D)
+    data = ppl.make_data(torch.from_numpy(x).cuda(), torch.from_numpy(y).cuda())
+    least = 256 + (-(-C // 256) * 240 + 255) // 256 * 256
+    full = ppl.ppl_workspace_size(ppl.PPL_MODEL_POLY, data, C, ppl.PPL_ALGO_MCMC)
+    T, got = 25, []
+    for size in (full, least):
+        out = dict(state=torch.empty((6, C), dtype=torch.float64, device="cuda"),
+                   accepts=torch.empty(C, dtype=torch.int64, device="cuda"),
+                   summaries=torch.empty(29, dtype=torch.float64, device="cuda"),
+                   scalars=torch.empty(4, dtype=torch.float64, device="cuda"),
+                   n_trace=torch.empty((T, C), dtype=torch.int8, device="cuda"),
+                   log_alpha=torch.empty((T, C), dtype=torch.float64, device="cuda"))
+        block = ppl.workspace(size + 256).fill_(0x5A)
+        ppl.ppl_mcmc(ppl.PPL_MODEL_POLY, data, C, T, 23, burn_in=5, ws=block[:size], **out)
+        assert torch.all(block[size:] == 0x5A)             # nothing written past the end
+        got.append({k: v.cpu().numpy() for k, v in out.items()})
+    for key in ("state", "accepts", "n_trace"):
+        np.testing.assert_array_equal(got[0][key], got[1][key], err_msg=key)
+    lw = torch.empty(C, dtype=torch.float64, device="cuda")
+    ppl.ppl_importance(ppl.PPL_MODEL_POLY, data, C, 23, log_weights=lw)      # chain c starts at execution c
+    size = np.abs(lw.cpu().numpy()) + np.cumsum(np.abs(got[0]["log_alpha"]) + 4.0, axis=0)
+    assert np.all(np.abs(got[0]["log_alpha"] - got[1]["log_alpha"]) <= (D + 4) * 2.0 ** -52 * size)
+    for key in ("summaries", "scalars"):
+        assert mixed_err(got[0][key], got[1][key]) < 1e-10, key
+    with pytest.raises(ppl.PplError) as e:
+        ppl.ppl_mcmc(ppl.PPL_MODEL_POLY, data, C, T, 23, ws=ppl.workspace(least)[:least - 1])
+    assert e.value.code == ppl.PPL_E_WORKSPACE
