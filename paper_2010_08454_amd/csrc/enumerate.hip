@@ -716,6 +716,27 @@ static int en_plan(int K, int T, EnPlan &p) {
     return PPL_OK;
 }
 
+// Workgroups of the sum kernel that a CU holds: 18 KB of LDS leave room for eight,
+// more than 128 vector registers for six (three waves per SIMD), more than 168 for four.
+constexpr int en_resident(int K, int ts) {
+    if (K >= 6) return ts >= 3 ? 4 : K == 7 && ts == 2 ? 6 : 8;
+    return ts * K > (K == 5 ? 19 : 20) ? 6 : 8;
+}
+
+// Workgroups of the walk, each with a record.  Every workgroup takes an equal share of
+// the tiles, so one more round of a few workgroups would leave most SIMDs idle (2048
+// workgroups where 1536 fit took 113 ms instead of 95 for 4 states x 20 steps): as
+// many as an MI355X's 256 CUs hold.  A constant and not the number that the device at
+// hand holds: the records decide how the FP64 sums are grouped, and the results
+// depend on the inputs only.
+constexpr int kEnCus = 256;
+static int en_records(const EnPlan &p, int K) { return std::min(p.grid, kEnCus * en_resident(K, p.Ts)); }
+
+int enum_records(int K, int T) {
+    EnPlan p;
+    return en_plan(K, T, p) ? 0 : en_records(p, K);
+}
+
 // Workspace: [256 scalars][le T K][glob 6][rec1 grid 2][rec2 grid (1 + T K)], each 256-byte aligned.
 size_t enum_ws_bytes(int K, int T) {
     EnPlan p;
@@ -724,28 +745,9 @@ size_t enum_ws_bytes(int K, int T) {
            align_up((size_t)p.grid * (1 + T * K) * 8, 256);
 }
 
-// Workgroups of the sum kernel that the device holds at once, at most p.grid:
-// every workgroup takes an equal share of the tiles, so one more round of a
-// few workgroups would leave most SIMDs idle (2048 workgroups where 1536 fit
-// took 113 ms instead of 95 for 4 states x 20 steps).
 template <int K, int TS>
-static int en_sum_grid(const EnPlan &p) {
-    static const int resident = [] {
-        int dev = 0, ncu = 0, per_cu = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, enum_sum_kernel<K, TS, en_ul(K, TS)>, kEnThreads, 0) !=
-                hipSuccess)
-            return 0;
-        return ncu * per_cu;
-    }();
-    return resident > 0 ? std::min(p.grid, resident) : p.grid;
-}
-
-template <int K, int TS>
-static int en_launch(const EnumDev &d, const EnPlan &p, int &nrec, hipStream_t st) {
+static int en_launch(const EnumDev &d, int nrec, hipStream_t st) {
     constexpr int UL = en_ul(K, TS);
-    nrec = en_sum_grid<K, TS>(p);
     static_assert(TS <= kEnMaxTS && TS * K * K <= kEnMaxF, "nested tables exceed their LDS slots");
     {
         KernelTimer timer("enum_sum_kernel", st);
@@ -765,8 +767,8 @@ static int en_launch(const EnumDev &d, const EnPlan &p, int &nrec, hipStream_t s
 }
 
 template <int K, int TS = en_ts_max(K)>
-static int en_dispatch(const EnumDev &d, const EnPlan &p, int &nrec, hipStream_t st) {
-    if (p.Ts == TS) return en_launch<K, TS>(d, p, nrec, st);
+static int en_dispatch(const EnumDev &d, const EnPlan &p, int nrec, hipStream_t st) {
+    if (p.Ts == TS) return en_launch<K, TS>(d, nrec, st);
     if constexpr (TS > 0) return en_dispatch<K, TS - 1>(d, p, nrec, st);
     return fail(PPL_E_UNSUPPORTED, "no enumeration kernel for %d states with %d nested sites", K, p.Ts);
 }
@@ -799,9 +801,10 @@ int run_enumerate_hmm(const EnumArgs &a, hipStream_t st) {
     for (int k = 0; k < K * K; ++k) d.lA[k] = log(a.A[k]);
     hipLaunchKernelGGL(enum_emission_kernel, dim3(1), dim3(256), 0, st, a.y, d, K, em, le, glob);
     PPL_LAUNCH_CHECK("enum_emission_kernel");
-    int rc = PPL_E_ARG, nrec = 0;
+    int rc = PPL_E_ARG;
+    const int nrec = en_records(p, K);
     switch (K) {
-        case 1: rc = en_launch<1, 0>(d, p, nrec, st); break;
+        case 1: rc = en_launch<1, 0>(d, nrec, st); break;
         case 2: rc = en_dispatch<2>(d, p, nrec, st); break;
         case 3: rc = en_dispatch<3>(d, p, nrec, st); break;
         case 4: rc = en_dispatch<4>(d, p, nrec, st); break;

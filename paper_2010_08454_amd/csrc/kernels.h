@@ -58,6 +58,7 @@ struct EnumArgs {
     void *ws;
 };
 size_t enum_ws_bytes(int K, int T);
+int enum_records(int K, int T);      // workgroups of the walk, and the groups its FP64 sums are taken in
 int run_enumerate_hmm(const EnumArgs &a, hipStream_t st);
 
 int run_philox(uint64_t seed, uint32_t c1, uint32_t c2, uint32_t c3, int64_t n, uint32_t *out, hipStream_t st);

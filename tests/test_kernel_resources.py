@@ -63,3 +63,21 @@ def test_chains_keep_their_tables_in_registers(kernels):
         k, = [k for n, k in kernels.items() if part in n]
         assert k[".private_segment_fixed_size"] == 0
         assert k[".group_segment_fixed_size"] == size
+
+
+def test_enumeration_sums_do_not_depend_on_the_device(kernels):
+    """The walk's workgroups, which group its FP64 sums, are a number of the
+    library's own for every state and step count (asked here without a device),
+    and it is the number that 256 CUs hold by the kernel's registers and LDS, at most
+    2048 and one per tile of 128 prefixes."""
+    import ctypes
+    records = ctypes.CDLL(LIB)._ZN3ppl12enum_recordsEii
+    for k in range(2, 9):
+        for t in (t for t in range(1, min(40, 1024 // (k * k)) + 1) if k ** t <= 2 ** 50):
+            nested = min({2: 12, 3: 7, 4: 6, 5: 5, 6: 5}.get(k, 4), t - 1)
+            part = f"enum_sum_kernelILi{k}ELi{nested}E"
+            kern, = [v for n, v in kernels.items() if part in n]
+            waves = 512 // (-(-kern[".vgpr_count"] // 8) * 8)              # per SIMD, 512 registers in eights
+            held = min(4 * waves // 2, 160 * 1024 // kern[".group_segment_fixed_size"])
+            tiles = -(-k ** (t - nested) // 128)
+            assert records(k, t) == min(tiles, 2048, 256 * held), (k, t)
