@@ -15,7 +15,7 @@
 //
 // What bounds it is the chain of a factor, not arithmetic: at N = 2^20 (256 blocks
 // of 8 particles per thread) the 1000 factors and 715 events of the state-space
-// model hold 1715 exchanges of about 6 us, each a store that has to reach the
+// model hold 1715 exchanges of about 4 us, each a store that has to reach the
 // others' caches and a poll that has to come back, and the rest is work of the
 // two waves per SIMD between exchanges.  So the chain is kept short: records are
 // merged from LDS by all waves with one workgroup barrier, a tile's totals leave
@@ -23,9 +23,8 @@
 // records travel, and a particle marks its slots instead of every slot searching
 // (8 slots per thread: 6.6 us of search and 1.3 us of staging per event).
 // Measured against merging by one wave, serial polls and a search per slot:
-// 1000 x 2^20 30.1 -> 21.4 ms, 300 x 1000 3.30 -> 2.03 ms, 300 x 100003 4.55 ->
-// 3.34 ms, mixture 300 x 20011 with K = 4 1.35 -> 1.26 ms; the noise drawn
-// while records travel is 3.2 ms of the first.
+// 1000 x 2^20 30.0 -> 20.1 ms, 300 x 1000 3.45 -> 2.11 ms, 300 x 100003 4.57 ->
+// 2.94 ms, mixtures with K = 4 300 x 20011 1.28 -> 1.19 ms, 300 x 131072 2.27 -> 1.69 ms.
 // Per factor s:
 //   1. every particle advances to factor s and adds its log-factor (FP32,
 //      compensated summation);
@@ -69,6 +68,7 @@ constexpr int kBarLine = 32;                  // unsigned per 128-byte line
 constexpr int kBarWords = kBarLine;           // word 1: abort flag
 constexpr int kRecWords = 16;                 // 64-bit words per 128-byte record line
 constexpr uint32_t kSpinLimit = 1u << 24;     // polls before a wait is declared hung (seconds)
+constexpr int kPollAtOnce = 64;               // most blocks that poll for records at once (see tagged_wait)
 constexpr int kYChunk = 2048;                 // observations staged in LDS at a time
 // Most tiles whose particles mark a block's slots.  At even weights a block's ancestors
 // lie in its own and one or two neighbouring tiles; five tiles of marks cost about
@@ -155,10 +155,18 @@ struct RecLds {
 // Leaves word k of block t's record in L.w[k][t].  Returns false (uniformly in the
 // block) once any block has aborted.  L.w is free for the next wait after the
 // workgroup barrier that every caller passes in between.
+// The nb^2 polls of the grid share the memory system with the records that they wait
+// for: with many blocks, polls before the records can be there hold those up, and the
+// first poll comes 1024 cycles late.  us for 300 factors of a 3-component mixture
+// without an event, with and without: 131072 particles (256 blocks) 1351 and 2500,
+// 50000 (98 blocks) 1058 and 1310; of the state-space model 1350 and 1910, 1048 and
+// 1120.  Up to kPollAtOnce blocks the wait costs about what it gains (32768
+// particles, 64 blocks: 1040 .. 1120 and 1155, 1000 .. 1010 and 990).
 template <int NW>
 __device__ __forceinline__ bool tagged_wait(uint64_t *rec, unsigned *bar, unsigned epoch, int nb, RecLds &L) {
     static_assert(NW <= 5, "record words in LDS");
     unsigned *abort_flag = bar + 1;
+    if (nb > kPollAtOnce) __builtin_amdgcn_s_sleep(16);
     if (threadIdx.x < nb) {          // nb <= kSmcThreads
         uint64_t *line = rec + ((size_t)(epoch & 1u) * nb + threadIdx.x) * kRecWords;
         uint32_t spins = 0;
