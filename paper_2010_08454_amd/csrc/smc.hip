@@ -71,8 +71,13 @@ constexpr uint32_t kSpinLimit = 1u << 24;     // polls before a wait is declared
 constexpr int kPollAtOnce = 64;               // most blocks that poll for records at once (see tagged_wait)
 constexpr int kYChunk = 2048;                 // observations staged in LDS at a time
 // Most tiles whose particles mark a block's slots.  At even weights a block's ancestors
-// lie in its own and one or two neighbouring tiles; five tiles of marks cost about
-// what the search in memory costs, which is left to ancestors that are strewn wider.
+// lie in its own and one or two neighbouring tiles; ancestors that are strewn wider are
+// left to a search in memory per slot.  The line is a number of tiles at every tile
+// size: us for 60 factors and 59 events of the state-space model with observations so
+// sharp that few particles keep weight, for at most 3, 5 and 16 tiles: 131072
+// particles (tiles of 512) 923, 915 and 1116; 262144 (1024) 1207, 1185 and (8) 1125;
+// 2^20 (4096) 2995, 2135 (3 and 5).  Staging up to 8192 prefix sums in LDS and searching
+// them took 1240, 1480 and 3550.
 constexpr int kScatterTiles = 5;
 constexpr int kBatchTries = 64;               // reloads of a batch of tagged words before polling them one by one
 
