@@ -132,9 +132,11 @@ def _ptr(t):
 
 
 def _stream(stream):
-    if stream is None:                      # torch.cuda.current_stream() without its Stream object
-        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
-    return stream.cuda_stream
+    if stream is not None:
+        return stream.cuda_stream
+    # torch.cuda.current_stream() without its Stream object, where torch has this (private) name
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    return torch.cuda.current_stream().cuda_stream if raw is None else raw(torch.cuda.current_device())
 
 
 def make_data(x, y, n_data=None, dim=0, hyper=None, dtype=None):

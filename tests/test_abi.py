@@ -198,3 +198,22 @@ def test_smc_stop_resume_validates(ppl):
     assert L.ppl_smc_checkpoint_bytes(ppl.PPL_MODEL_GMM, ctypes.byref(g), 1000, ctypes.byref(b)) == 0
     assert b.value >= 256 + 12 * 1000 * 4
     assert L.ppl_smc_checkpoint_bytes(ppl.PPL_MODEL_BLR, ctypes.byref(g), 1000, ctypes.byref(b)) == ppl.PPL_E_MODEL
+
+
+def test_current_stream_without_the_private_name(ppl, monkeypatch):
+    """A torch without the raw-stream function gives its current stream's handle; a
+    stream that the caller passes is used as it is."""
+    import types
+
+    import torch
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=0x1234))
+    assert ppl._stream(None) == 0x1234
+    assert ppl._stream(types.SimpleNamespace(cuda_stream=0x5678)) == 0x5678
+
+
+def test_every_entry_point_declares_its_arguments(ppl):
+    """Pointers are passed as plain integers, which a function without declared
+    argument types would take as 32-bit values."""
+    for name in ppl.EXPORTS:
+        assert getattr(ppl.lib, name).argtypes is not None or name == "ppl_last_error" or name.endswith("version"), name
