@@ -72,6 +72,51 @@ def test_blr_nonfinite_rows(ppl, n, row):
         assert np.all(np.isneginf(lw)) if value == np.inf else np.all(np.isnan(lw))
 
 
+@pytest.mark.parametrize("kind", ["ordinary", "subnormal", "huge", "infinite", "nan"])
+@pytest.mark.parametrize("dim", [4, 8, 12, 16])
+def test_blr_matrix_rows_equal_the_scalar_chain(ppl, dim, kind):
+    """31 rows among rows of zeros (which add a square of zero): in either half of a
+    64-row tile they run on the matrix cores, after the last 32 rows a lane forms the
+    chain fma(-x_k, w_k, r) itself.  Every log-weight has the same bits wherever the
+    rows lie, at each launch shape.  Subnormal entries meet latents of size 1e20 and a
+    noise of 1e-20, which make them visible."""
+    import torch
+    D = 16 * 64 + 63
+    g = np.random.default_rng(dim)
+    rows = g.standard_normal((31, dim)).astype(np.float32)
+    target = g.standard_normal(31).astype(np.float32)
+    hyper = [1.0, 0.5]
+    if kind == "subnormal":
+        rows = (rows * np.float32(1e-20)) * np.float32(1e-20)
+        assert np.all(np.abs(rows) < np.finfo(np.float32).tiny)
+        target[:] = 0.0
+        hyper = [1e20, 1e-20]
+    elif kind == "huge":
+        rows[::3] *= np.float32(1e18)
+        rows[1::3] *= np.float32(1e-18)
+    elif kind in ("infinite", "nan"):
+        rows[5, dim - 2] = np.inf if kind == "infinite" else np.nan
+    for n in (100, 20_000, 100_000, 400_000, 600_000):
+        ref = None
+        for at in (16 * 64 + 32, 0, 32, 15 * 64, 15 * 64 + 32, 16 * 64):     # the scalar chain, then the matrix cores
+            X, y = np.zeros((D, dim), np.float32), np.zeros(D, np.float32)
+            X[at:at + 31], y[at:at + 31] = rows, target
+            data = ppl.make_data(torch.from_numpy(X).cuda(), torch.from_numpy(y).cuda(), dim=dim, hyper=hyper)
+            lw = torch.empty(n, dtype=torch.float64, device="cuda")
+            ppl.ppl_importance(ppl.PPL_MODEL_BLR, data, n, 7, log_weights=lw)
+            lw = lw.cpu().numpy()
+            if ref is None:
+                ref = lw
+                if kind in ("ordinary", "subnormal"):
+                    assert np.all(np.isfinite(lw))
+                if kind in ("ordinary", "subnormal", "huge"):      # (a few huge squares exceed FP32)
+                    assert np.unique(lw).size > 0.9 * n
+            if kind == "nan":
+                assert np.all(np.isnan(lw)) and np.all(np.isnan(ref))
+            else:
+                np.testing.assert_array_equal(lw.view(np.int64), ref.view(np.int64))
+
+
 # ------------------------------------------------------ FP64 Box-Muller --
 @pytest.mark.parametrize("seed", [1, 2 ** 63 + 5])
 def test_poly_draws_64bit(ppl, seed):
