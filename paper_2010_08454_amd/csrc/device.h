@@ -222,11 +222,6 @@ __device__ __forceinline__ double wave_max(double v) {
     for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, 64));
     return v;
 }
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-    return v;
-}
 // Wave-wide FP32 reductions through DPP row operations (full-rate VALU
 // moves, no LDS permute): two quad permutations, the half-row and row
 // mirrors, then the row-15 and row-31 broadcasts (rows left out of a
