@@ -9,12 +9,11 @@ timed region.  The metric is particle-likelihood evaluations per second
 
 Printed as one JSON line, with
   roofline     -- the dominant kernel (blr_is_kernel) timed with HIP events on
-                  its launch stream during the timed steps, against MI355X's
-                  published FP32 vector peak (157.3 TFLOP/s, packed FP32), with
-                  the fraction of the unpacked FMA issue ceiling the library can
-                  reach (it is compiled without packed FP32) beside it as frac_attainable:
-                  algorithmic work 34 FLOP per evaluation (16 FMA residual +
-                  1 FMA square-accumulate);
+                  its launch stream during the timed steps: the 32 FLOP per
+                  evaluation of the residual (16 FMA) against MI355X's published
+                  FP32 matrix rate (157.3 TFLOP/s), where they run, and beside
+                  them as "vector" the 2 FLOP of the square against the vector
+                  units' rate without packed FP32 (78.64 TFLOP/s);
   cpu_baseline -- the CPU oracle on a bounded sample of the same workload.
 
 Other configurations print the same fields for their own workload:
@@ -28,8 +27,8 @@ Other configurations print the same fields for their own workload:
                     iterations per second
   enum-hmm          exact inference by enumeration: every path of a 4-state
                     hidden Markov model over 20 steps (2^40 paths, FP64), paths
-                    per second; roofline of the summing pass (two FMA per path)
-                    against the FP64 vector peak
+                    per second; roofline of the walk's sums (2 + 1/K FLOP per
+                    path) against the FP64 vector peak
   lgssm             bootstrap SMC on the linear-Gaussian state space model
   gmm-batched       batched SMC over 256 mixture instances (autotuned first)
   resample-gather   resampling fused with the state gather, roofline against HBM
@@ -58,7 +57,8 @@ FP32_VALU_PUBLISHED_TFLOPS = 157.3        # the matrix cores' FP32 rate too; on 
                                           # FP32, which the library's compile flags disable
 FP64_VALU_TFLOPS = 78.6
 
-FLOP_PER_EVAL_BLR = 34                    # 17 FMA per (particle, row) at d = 16
+FLOP_PER_EVAL_BLR = 32                    # 16 FMA per (particle, row) at d = 16 on the matrix cores,
+SQUARE_FLOP_PER_EVAL_BLR = 2              # and one on the vector units
 # Committed PMC byte counts per configuration: (summary file under profiles/, the
 # sources whose hash keys it).  A count is used only while the hash matches.
 _CS = "paper_2010_08454_amd/csrc/"
@@ -961,11 +961,12 @@ def main():
                 "kernel": kname, "kernel_ms": round(k_avg_ms, 4), "kernel_launches": k_n,
                 "flop_per_launch": flop_per_launch}
     if args.config == "blr":
+        squares = SQUARE_FLOP_PER_EVAL_BLR * N * D / (k_avg_ms / 1e3) / 1e12
         roofline["peak_note"] = ("peak is MI355X's published FP32 rate, which the matrix cores reach with FP32 "
-                                 "operands (256 CU x 256 FLOP x 2.4 GHz); the residual products run there, the "
-                                 "squares on the vector units beside them (78.64 TFLOP/s without packed FP32)")
-        roofline["peak_attainable"] = round(FP32_VALU_PUBLISHED_TFLOPS, 2)
-        roofline["frac_attainable"] = round(achieved / FP32_VALU_PUBLISHED_TFLOPS, 4)
+                                 "operands (256 CU x 256 FLOP x 2.4 GHz); the residual products, counted here, run "
+                                 "there, the squares on the vector units beside them")
+        roofline["vector"] = {"achieved": round(squares, 3), "peak": round(FP32_VALU_UNPACKED_TFLOPS, 2),
+                              "unit": unit, "frac": round(squares / FP32_VALU_UNPACKED_TFLOPS, 4)}
 
     out = {"metric": "particle-likelihood evals/s", "value": value, "unit": "evals/s", "n_gpus": 1,
            "steps": args.steps, "warmup": args.warmup, "ms_per_step": round(ms_per_step, 4),
