@@ -30,7 +30,9 @@
  *     counter = (particle or slot index, block index, step, instance << 8 | tag)
  *     with tags 0 = prior, 1 = proposal, 2 = resampling, 4 = simulated
  *     training pairs, 5 = network initialisation.  Results depend only on
- *     (seed, inputs), never on the launch configuration.
+ *     (seed, inputs), never on the launch configuration of a device; the sizes
+ *     of a call are inputs, and FP64 sums may be grouped by them (a particle's
+ *     log-weight can differ in its last bits between calls of different N).
  */
 #ifndef PPL_H
 #define PPL_H
@@ -345,11 +347,11 @@ typedef struct ppl_mcmc_result {
 } ppl_mcmc_result;
 
 /* Lightweight Metropolis-Hastings (paper Sec. 3.6.3): n_chains independent
- * chains of n_iters iterations, one chain per GPU lane.  A chain's trace is
- * the set of sites its execution reached; an iteration picks one uniformly,
- * resamples it from its prior and re-executes the model, keeping the values
- * of sites both executions reach, drawing sites only the new one reaches
- * fresh from their prior and dropping the others; accepted when
+ * chains of n_iters iterations, on one GPU lane each or, for few chains, four.
+ * A chain's trace is the set of sites its execution reached; an iteration
+ * picks one uniformly, resamples it from its prior and re-executes the model,
+ * keeping the values of sites both executions reach, drawing sites only the
+ * new one reaches fresh from their prior and dropping the others; accepted when
  * log v < log L(x') - log L(x) + log |trace(x)| - log |trace(x')|.
  * model: PPL_MODEL_POLY (trace n, c_0..c_{n-1}; data and hyper-parameters as
  * for importance sampling).  Words of iteration t of chain c (tag 8): block
@@ -382,11 +384,12 @@ typedef struct ppl_enum_result {
 
 /* Exact inference by enumeration (paper Sec. 3.6.1): every execution of the
  * model, i.e. every path z in {0..K-1}^T, weighted by the product of its
- * sample probabilities and its factors; Z = sum_z exp(lw(z)).  Every path is
- * evaluated (no dynamic programming over the chain structure).  Sums are FP64
- * relative to the largest log-weight; a NaN log-weight makes the status
- * PPL_E_NONFINITE and log Z NaN; all weights zero: PPL_E_ZERO_WEIGHT and
- * log Z = -inf.  model: PPL_MODEL_HMM; K^T <= 2^50.  Workspace:
+ * sample probabilities and its factors; Z = sum_z exp(lw(z)).  Every path's
+ * weight is formed and added; a recursion over the chain (the largest
+ * log-weight up to rounding) only sets the scale that the FP64 sums are taken
+ * in.  A NaN log-weight makes the status PPL_E_NONFINITE and log Z NaN; all
+ * weights zero: PPL_E_ZERO_WEIGHT and log Z = -inf.  model: PPL_MODEL_HMM;
+ * K^T <= 2^50.  Workspace:
  * ppl_workspace_size(PPL_MODEL_HMM, data, 1, PPL_ALGO_ENUM).  With sync_host
  * the call blocks on the stream and returns the device status. */
 int ppl_enumerate(int model, const ppl_data *data, void *d_ws, size_t ws_bytes, void *stream, ppl_enum_result *out);

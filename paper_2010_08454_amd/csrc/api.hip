@@ -842,6 +842,9 @@ static int train_graph(const TrainPlan &p, uint64_t seed, const MlpView &w, cons
     return rc;
 }
 
+// {scalars, 256 bytes | spare | decoded q | partial records}.  The spare part held a
+// batch's activations when the network ran as separate products; nothing uses it, and
+// it stays so that sizes and offsets do not change.
 static size_t infer_ws_bytes(int model, int64_t n) {
     return 256 + align_up(train_ws_bytes(64), 256) + 256 * 8 /* decoded q, <= 332 doubles */ * 2 +
            align_up(prop_partial_bytes(model, n), 256);

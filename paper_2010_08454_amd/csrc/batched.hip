@@ -228,7 +228,12 @@ __device__ __forceinline__ void bt_init(uint32_t j, uint32_t c3, Key key, float 
 constexpr float kBtTiny = 1e-30f;
 constexpr float kBtHalfLog2e = 0x1.715476p-1f;    // log2(e) / 2
 
-// log x for normal positive x: log2(x) times ln 2 in two parts (a NaN stays NaN).
+// log x for normal positive x (a NaN stays NaN): l = log2(x) from the hardware, times
+// ln 2 in two parts.  The rounding error of l hi is added although the outer fma is
+// exact in that product, so it counts twice: up to 0.95 units in the last place where
+// fmaf(l, hi, l lo) would err by 0.50.  These are the bits that the factor had with the
+// library's __logf, and they stay: a filter resamples on the sums of these factors,
+// and one other rounding is another ancestor and from there another run.
 __device__ __forceinline__ float bt_log_normal(float x) {
     const float hi = 0x1.62e42ep-1f, lo = 0x1.efa39ep-25f;
     const float l = __builtin_amdgcn_logf(x);

@@ -2,9 +2,9 @@
 //
 // Each thread owns P particles.  A particle draws its latents at the model's
 // sample sites, accumulates its factors over the data, and its log-weight is
-// folded into a per-block FP64 partial {max, sum e, sum e^2, sum e f}; a
-// one-wave finalize kernel merges the block partials in a fixed order and
-// writes log Z-hat = LSE - log N, the ESS and the posterior summaries.
+// folded into a per-block FP64 partial {max, sum e, sum e^2, sum e f}; one
+// workgroup (weights_finalize_kernel) merges the block partials in a fixed order
+// and writes log Z-hat = LSE - log N, the ESS and the posterior summaries.
 //
 // Data are the same for every lane of a wave (all lanes process the same datum
 // for different particles): scalar loads bring them into SGPRs, and the rows of
@@ -37,8 +37,9 @@ constexpr int kIsWaves = kIsThreads / 64;
 // squares within 32 rows keep their order too.  The matrix cores take FP32 at
 // 256 FLOP per cycle and CU, the vector units at 128 without packed FP32.
 // Measured at 2^20 particles x 10^4 rows, d = 16: 2.67 ms a call against 4.89 for
-// the same chain on the vector units (0.95 of their rate), 134 of the matrix
-// cores' 157 TFLOP/s.  Bound: matrix-core issue; the squares run beside it.
+// the same chain on the vector units (0.95 of their rate): 32 FLOP per particle
+// and row on the matrix cores, 126 of their 157 TFLOP/s.  Bound: matrix-core issue;
+// the squares run beside it on the vector units.
 typedef float blr_f32x4 __attribute__((ext_vector_type(4)));
 typedef float blr_row4 __attribute__((ext_vector_type(4), aligned(4)));   // data rows are 4-byte aligned
 
@@ -399,7 +400,7 @@ static int launch_blr(const IsArgs &a, hipStream_t st) {
 // Launch shape of the polynomial model.  Up to 2^15 particles a quad of lanes
 // per particle (at most two waves per SIMD so; the records of 64 particles fit
 // the workspace beside one of 256 by the same count as in blr_shape); above, a
-// lane per particle, and from 2^19 on four, which share the point loads and the
+// lane per particle, and from 2^18 on four, which share the point loads and the
 // workgroup's reduction.
 static int launch_poly(const IsArgs &a, hipStream_t st) {
     const int64_t per = a.N <= 32768 ? kQuadParticles : a.N < 262144 ? kIsThreads : 4 * kIsThreads;
