@@ -70,7 +70,7 @@ __global__ __launch_bounds__(kSumThreads, 1) void infer_net_kernel(const void *_
     __shared__ double tot[kPolyAcc];
     __shared__ double s[kSummaryDim];
     __shared__ double red[kSumWaves];
-    __shared__ int hist[32];
+    __shared__ int hist[32], nan_seen;
     __shared__ __align__(16) uint16_t row[3][kMlpHid];
     __shared__ float out[kMlpOut];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -96,6 +96,7 @@ __global__ __launch_bounds__(kSumThreads, 1) void infer_net_kernel(const void *_
     } else {
         const float *Y = (const float *)yv;
         if (tid < 32) hist[tid] = 0;
+        if (tid == 0) nan_seen = 0;
         __syncthreads();
         double sum_y = 0.0;
         for (int64_t d = tid; d < D; d += kSumThreads) {
@@ -103,10 +104,12 @@ __global__ __launch_bounds__(kSumThreads, 1) void infer_net_kernel(const void *_
             ysf[d] = yf;
             sum_y += (double)yf;
             gmm_bin(hist, (double)yf);
+            if (yf != yf) nan_seen = 1;
         }
         load_weights();
         __syncthreads();
         gmm_finish(ysf, D, hist, sum_y, red, s);
+        if (nan_seen && tid < 16) s[tid] = NAN;      // a NaN has no rank: the order statistics are undefined
     }
     if (tid < kSummaryDim) {
         row[0][tid] = f32_to_bf16((float)s[tid]);

@@ -535,3 +535,25 @@ def test_fragment_order_copies_follow_adam(ppl):
         finally:
             del os.environ["PPL_TRAIN_UNFUSED"]
     np.testing.assert_array_equal(res[0], res[1])
+
+
+@pytest.mark.parametrize("D", [1, 2, 17, 1000])
+def test_mixture_summaries_with_a_nan_datum(ppl, D):
+    """A NaN has no rank, so every order statistic is NaN (and not what the memory
+    held before: the second call follows one on other data); the weights' status
+    says so."""
+    import torch
+    w = ppl.ppl_proposal_init(3)
+    g = np.random.default_rng(D)
+    y = g.standard_normal(D).astype(np.float32)
+    y[D // 2] = np.nan
+    clean = torch.from_numpy(g.standard_normal(8192).astype(np.float32)).cuda()
+    for before in (False, True):
+        if before:
+            ppl.ppl_proposal_infer(ppl.PPL_MODEL_GMM, ppl.make_data(None, clean, dim=3, dtype=ppl.PPL_F32), w, 64, 1)
+        s = torch.empty(64, dtype=torch.float64, device="cuda")
+        scal = torch.empty(8, dtype=torch.float64, device="cuda")
+        ppl.ppl_proposal_infer(ppl.PPL_MODEL_GMM, ppl.make_data(None, torch.from_numpy(y).cuda(), dim=3, dtype=ppl.PPL_F32),
+                               w, 64, 1, data_summaries=s, scalars=scal)
+        assert torch.isnan(s[:16]).all()
+        assert int(scal[3]) == ppl.PPL_E_NONFINITE
